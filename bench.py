@@ -38,7 +38,7 @@ HBM_PEAK_GBS = 8000.0
 VALU_PEAK_GWIS = 256 * 2.4
 CSRC = os.path.join(ROOT, "paper_1911_13214_amd", "csrc")
 # the sources of the fill kernels, whose digest the counter records carry
-FILL_SOURCES = [os.path.join(CSRC, f) for f in ("rotor_paths.h", "rotor_fill.hip", "rotor_rows.h", "rotor_rows_0.hip",
+FILL_SOURCES = [os.path.join(CSRC, f) for f in ("rotor_paths.h", "rotor_fill.hip", "rotor_tile.hip", "rotor_rows.h", "rotor_rows_0.hip",
                                                 "rotor_rows_1.hip", "rotor_rows_2.hip", "rotor_rows_3.hip")]
 
 

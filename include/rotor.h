@@ -232,12 +232,13 @@ ROTOR_API int32_t rotor_solve_status(const void *d_work, uint64_t work_bytes, in
  *                            least 256 blocks over all chains, else by
  *                            anti-diagonals (30 short launches); the fast
  *                            order for large tables.
- *   ROTOR_SCHEDULE_DIAGONAL  one launch per t - s over all pairs (the
- *                            wavefront the recurrence allows), the splits of
- *                            a pair spread over four waves from t - s = 16 on;
- *                            fewer launches, the fast order for small tables.
- *   ROTOR_SCHEDULE_AUTO      DIAGONAL when the table has at most 2e9 split
- *                            candidates (L^3/6 (M+1)) for one chain, or 4e8
+ *   ROTOR_SCHEDULE_DIAGONAL  4 x 4 tiles of pairs, one launch per
+ *                            tile-diagonal (ceil(L / 4) of them), the splits
+ *                            that a tile shares as register products; few
+ *                            launches, the fast order for small tables.
+ *   ROTOR_SCHEDULE_AUTO      DIAGONAL when the table has at most 2e10 split
+ *                            candidates (L^3/6 (M+1)) for one chain with
+ *                            M < 1024, 6e9 for one with more budgets, 4e9
  *                            summed over a batch, or when one chain has
  *                            M < 63; BLOCKED otherwise (the order rotor_solve
  *                            uses).

@@ -107,6 +107,11 @@ struct LaunchObserver {
 hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_t stream,
                        LaunchObserver *obs = nullptr, bool side_stream = true);
 
+// Side of the tiles of the streamed fill, in stages, and the launch of one
+// of its tile-diagonals (level = 0: the diagonal tiles with the leaves).
+constexpr int kTileSide = 4;
+void launch_tiles(int level, hipStream_t stream, const Tables &tb, const Work &w);
+
 // Edges of the blocked fill by rows: whether a block-diagonal with `blocks`
 // blocks over all chains takes them, and the launch of row 16(I + 1) - a of
 // its `blocks` blocks (I, I + delta) per chain (finish: the middle kernels

@@ -86,7 +86,19 @@ __device__ inline uint32_t load32(const uint32_t *row, int m)
 }
 
 __device__ inline uint32_t sat_add(uint32_t a, uint32_t b) { return __builtin_elementwise_add_sat(a, b); }
+// v << S for a value below 2^(32 - S); an infinity (all ones) stays all ones.
+__device__ inline uint32_t rot_left(uint32_t v, int S) { return __builtin_amdgcn_alignbit(v, v, (32 - S) & 31); }
 __device__ inline uint64_t umin(uint64_t a, uint64_t b) { return b < a ? b : a; }
+
+// Minimum of two doubles that are never NaN: v_min_f64 itself (the
+// compiler's minnum quiets its operands first, one more instruction per
+// candidate)
+__device__ __forceinline__ double min_f64(double a, double b)
+{
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
 
 // Per-chain views of the workspace.
 struct ChainWork {

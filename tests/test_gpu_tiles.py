@@ -1,0 +1,51 @@
+"""The streamed order's 4 x 4 tiles at the sizes where they can go wrong,
+against the oracle: chains that end inside a tile, the first chains with inner
+splits, budgets around a wave and around a workgroup's window of 1024, shifts
+beyond a window, and the three kinds of keys."""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from paper_1911_13214_amd import chaingen
+
+pytestmark = pytest.mark.gpu
+
+
+def check(params, M, schedule="diagonal"):
+    from gpu_util import chain_tables, solve_on_gpu
+
+    print(f"tiles L={params.shape[-1]} M={M} n={params.shape[0]} {schedule}", flush=True)
+    _, cost, dec = solve_on_gpu(params, M, schedule=schedule)
+    for c in range(params.shape[0]):
+        C, D = orc.solve(params[c], M)
+        gc, gd = chain_tables(cost, dec, c, params.shape[-1], M)
+        assert np.array_equal(gc, C) and np.array_equal(gd, D), c
+
+
+# costs x 2^0: 32-bit keys; x 2^14 (L = 70): 4-byte values that leave no room
+# for them; x 2^26: 64-bit values
+@pytest.mark.parametrize("shift", [0, 14, 26])
+@pytest.mark.parametrize("L,M", [(1, 0), (2, 64), (3, 63), (4, 65), (5, 127), (8, 128), (9, 200), (12, 191), (13, 192),
+                                 (16, 300), (17, 301), (29, 511), (70, 257)])
+def test_tile_edges(L, M, shift):
+    p = chaingen.random_chains(2, L, seed=100 + L)
+    p[:, :2] <<= shift
+    check(p, M)
+
+
+# windows of 1024 budgets: just one, a second of one budget, several; sizes up
+# to 700 reach past a whole window of a smaller workgroup, and 1500 past one of
+# 1024
+@pytest.mark.parametrize("scale", [1, 70, 150])
+@pytest.mark.parametrize("L,M", [(14, 1023), (14, 1024), (21, 1100), (10, 3100)])
+def test_tile_windows(L, M, scale):
+    p = chaingen.random_chains(1, L, seed=200 + L)
+    p[:, 2:] *= scale
+    check(p, M)
+
+
+def test_inner_runs():
+    # 32-bit keys with 4 to 5 split bits: runs of 16 and 32 splits
+    p = chaingen.random_chains(1, 150, seed=7)
+    p[:, :2] *= 230
+    check(p, 90)
