@@ -85,22 +85,35 @@
 namespace rotor {
 namespace {
 
-// The automatic schedule streams tables of up to 2e10 split candidates for one
-// chain, or 4e9 over a batch, tile-diagonal by tile-diagonal (rotor_tile.hip).
-// Measured on MI355X, blocked against streamed: L = 339, M = 500 (3e9)
-// 5.7 / 1.9 ms; L = 500, M = 500 (1e10) 8.3 / 4.8 ms; L = 500, M = 1000 (2e10)
-// 9.2 / 8.9 ms; L = 500, M = 2000 (4e10) 11.6 / 17.5 ms; 32 chains of L = 64,
-// M = 640 (9e8) 1.1 / 0.64 ms; 64 chains of L = 130, M = 1000 on the 64-bit path
-// (2e10) 17.0 / 18.6 ms.  The streamed order takes 2 bytes of operands per
-// candidate past the L2 (4 on the 64-bit path), the blocked one a sixth of that
-// but 30 launches per 16 stages; past 1024 budgets a tile takes several windows
-// in turn and the line is lower (L = 303, M = 2000, 9e9: 5.2 / 4.0 ms, on the
-// 64-bit path 7.0 / 7.4 ms).  Any single chain with fewer than 64 budgets is streamed: they
+// The automatic schedule streams small tables.  By tiles, up to 2e10 split
+// candidates for one chain (1e10 from 1024 budgets on) and 4e9 over a batch;
+// measured on MI355X, blocked against tiles: L = 339, M = 500 (3e9) 5.7 / 1.9 ms;
+// L = 500, M = 500 (1e10) 8.3 / 4.8 ms; L = 500, M = 1000 (2e10) 9.2 / 8.7 ms;
+// L = 500, M = 2000 (4e10) 11.6 / 17.5 ms; L = 303, M = 2000 (9e9) 5.2 / 4.0 ms, on
+// the 64-bit path 7.0 / 7.0 ms; 32 chains of L = 64, M = 640 (9e8) 1.1 / 0.64 ms;
+// 64 chains of L = 130, M = 1000 on the 64-bit path (2e10) 17.0 / 18.6 ms.  The
+// tiles take 2 bytes of operands per candidate past the L2 (4 on the 64-bit
+// path), the blocked order a sixth of that but 30 launches per 16 stages.  By
+// diagonals (tiles_take), up to 2e9 for one chain (L = 250 at M = 500) and 4e8
+// for a batch.  Any single chain with fewer than 64 budgets is streamed: they
 // leave most lanes of the blocked kernels' 64-budget chunks idle.
-constexpr uint64_t kStreamMaxCandidates1 = 20000000000ull;
-constexpr uint64_t kStreamMaxCandidatesN = 4000000000ull;
-constexpr uint64_t kStreamMaxCandidatesWindows = 6000000000ull;
+constexpr uint64_t kTileMaxCandidates1 = 20000000000ull;
+constexpr uint64_t kTileMaxCandidatesWindows = 10000000000ull;
+constexpr uint64_t kTileMaxCandidatesN = 4000000000ull;
+constexpr uint64_t kStreamMaxCandidates1 = 2000000000ull;
+constexpr uint64_t kStreamMaxCandidatesN = 400000000ull;
 constexpr int kStreamBelowBudgets = 64;
+
+// The streamed order goes by tiles unless the budgets are so many, against the
+// stages, that sizes taken from them (a chain's sizes add up to about the
+// budgets, more where its memory is short) would reach past the tiles'
+// overlapping windows, which are then filled in turn: it then goes diagonal by
+// diagonal, one launch each (measured on MI355X, tiles against diagonals:
+// L = 100, M = 5000 2.3 / 1.4 ms, L = 60, M = 3000 0.78 / 0.34 ms, L = 20, M = 1431
+// 144 / 92 us; L = 200, M = 3000 1.8 / 3.3 ms, L = 100, M = 1000 0.32 / 0.51 ms).
+constexpr int kTileBudgets = 512, kTileBudgetsPerStage = 24;
+bool tiles_take(int L, int M) { return M < kTileBudgets || M <= kTileBudgetsPerStage * L; }
+constexpr int kSplitMinD = 16;  // diagonals from this length spread their splits over four waves
 
 // ---------------------------------------------------------------------------
 
@@ -805,17 +818,20 @@ __device__ __forceinline__ void diag_body(const ChainRows &r, const ChainWork &c
     }
 }
 
-// The pairs (s, s + d) inside the 16 x 16 diagonal blocks, kDiagBudgets
-// budgets per lane.
+// The pairs (s, s + d): inside the 16 x 16 diagonal blocks only (blocked
+// fill), or all of them (streamed fill of a small table, one launch per d).
+// NB budgets per lane: kDiagBudgets for the diagonal blocks of the blocked
+// order, kEdgeBudgets for the streamed order (small tables, where more and
+// smaller workgroups are faster).
+template <int NB>
 __global__ __launch_bounds__(kEdgeThreads) void diag_kernel(const int64_t *__restrict__ params, int L, int M,
-                                                   int64_t pitch, int64_t rows, int d,
+                                                   int64_t pitch, int64_t rows, int d, int whole,
                                                    int64_t *__restrict__ cost, int16_t *__restrict__ dec, Work w)
 {
     const int c = blockIdx.z;
     const int s = blockIdx.y + 1;
-    constexpr int NB = kDiagBudgets;
     const int t = s + d;
-    if ((s - 1) / kT != (t - 1) / kT)
+    if (!whole && (s - 1) / kT != (t - 1) / kT)
         return;
     const int m0 = blockIdx.x * (kEdgeThreads * NB) + threadIdx.x;
     if (m0 > M)
@@ -824,15 +840,90 @@ __global__ __launch_bounds__(kEdgeThreads) void diag_kernel(const int64_t *__res
     const ChainWork cw = chain_work(w, L, rows, pitch, c);
     int64_t *tab = cost + (int64_t)c * rows * pitch;
     int16_t *dtab = dec + (int64_t)c * rows * pitch;
+    const int D = block_diag(s, t);
     // the path and the saturation test first: their scalar loads go together
-    const bool narrow = cw.narrow(0), d16 = cw.diag16();
+    const bool narrow = cw.narrow(D), d16 = cw.diag16();
     const bool sat = saturated(r, cw, s, row_of(L, s, t), blockIdx.x * (kEdgeThreads * NB));
     if (!narrow)
         diag_body<Wide, false, NB>(r, cw, L, M, m0, pitch, s, t, sat, tab, dtab);
-    else if (d16)
+    else if (D == 0 && d16)
         diag_body<Narrow, true, NB>(r, cw, L, M, m0, pitch, s, t, sat, tab, dtab);
     else
         diag_body<Narrow, false, NB>(r, cw, L, M, m0, pitch, s, t, sat, tab, dtab);
+}
+
+// Streamed order for the longer diagonals: the d splits of each pair are
+// spread over the four waves of a workgroup (one pair, 64 budgets), wave w
+// taking the w-th quarter in increasing order; wave 0 then folds the four
+// results in split order (so ties still go to the smallest split), adds C_2
+// and the gates, and writes the cell.  Four times the waves of diag_kernel,
+// each with a quarter of the dependent loads.
+template <class P>
+__device__ __forceinline__ void diag_split_body(const ChainRows &r, const ChainWork &cw, int L, int M, int m,
+                                                int64_t pitch, int s, int t, int wave, bool sat, int64_t (*part)[64],
+                                                int64_t *tab, int16_t *dtab)
+{
+    const int mc = m <= M ? m : M;  // lanes past M load in bounds and store nothing
+    const int lane = threadIdx.x & 63;
+    const int64_t cell = row_of(L, s, t);
+    // every budget of the workgroup saturated (the same test in its four
+    // waves, so all of them leave before the barrier)
+    if (sat) {
+        if (wave == 0 && m <= M)
+            store_cell<P>(tab, dtab, cw.shadow, cell * pitch + m, P::all_only(least_time(cw, s, t)));
+        return;
+    }
+    const int d = t - s;
+    const int chunk = (d + 3) / 4;
+    const int k0 = s + wave * chunk;
+    const int k1 = min(t - 1, k0 + chunk - 1);
+    typename P::Acc acc;
+    P::init(acc);
+    if (k0 <= k1) {
+        uint64_t prefix = (uint64_t)(cw.pre[k0 - 1] - cw.pre[s - 1]);
+        RowCursor cur = row_cursor<P>(tab, cw.shadow, L, pitch, s, t, k0);
+        for (int kk = k0; kk <= k1; kk += kT - 1)
+            relax_run<P>(acc, r, mc, kk, min(kT - 1, k1 - kk + 1), cur, prefix);
+    }
+    part[wave][lane] = P::stored(acc);
+    __syncthreads();
+    if (wave != 0 || m > M)
+        return;
+#pragma unroll
+    for (int v = 1; v < 4; ++v)
+        P::merge_later(acc, part[v][lane]);
+    const int ri = m - r.wabar[s - 1];
+    const bool all_ok = m >= cw.gall[cell] && ri >= 0;
+    const int64_t below = row_of(L, s + 1, t) * pitch;
+    const typename P::Raw c2 = P::load(tab + below, cw.shadow + below, all_ok ? ri : m);
+    if (m < cw.gnone[cell])
+        P::init(acc);
+    if (all_ok)
+        P::relax_all(acc, c2, (uint64_t)(r.uf[s - 1] + r.ub[s - 1]));
+    store_cell<P>(tab, dtab, cw.shadow, cell * pitch + m, acc);
+}
+
+__global__ __launch_bounds__(256) void diag_split_kernel(const int64_t *__restrict__ params, int L, int M,
+                                                         int64_t pitch, int64_t rows, int d,
+                                                         int64_t *__restrict__ cost, int16_t *__restrict__ dec,
+                                                         Work w)
+{
+    __shared__ int64_t part[4][64];
+    const int c = blockIdx.z;
+    const int s = blockIdx.y + 1;
+    const int t = s + d;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m = blockIdx.x * 64 + (threadIdx.x & 63);
+    const ChainRows r = chain_rows(params, w, L, c);
+    const ChainWork cw = chain_work(w, L, rows, pitch, c);
+    int64_t *tab = cost + (int64_t)c * rows * pitch;
+    int16_t *dtab = dec + (int64_t)c * rows * pitch;
+    const bool narrow = cw.narrow(block_diag(s, t));
+    const bool sat = saturated(r, cw, s, row_of(L, s, t), blockIdx.x * 64);
+    if (narrow)
+        diag_split_body<Narrow>(r, cw, L, M, m, pitch, s, t, wave, sat, part, tab, dtab);
+    else
+        diag_split_body<Wide>(r, cw, L, M, m, pitch, s, t, wave, sat, part, tab, dtab);
 }
 
 // The corner cell (16I + 16, 16J + 1) of a block (I, J) has no low or high
@@ -1941,12 +2032,15 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
     // A small table goes tile-diagonal by tile-diagonal, in one launch per four
     // stages; the blocked fill would need 33 per sixteen.
     const uint64_t r_total = ((uint64_t)L * L * L / 6) * W * nc;
-    const bool streamed = schedule == ROTOR_SCHEDULE_DIAGONAL ||
-                          (schedule == ROTOR_SCHEDULE_AUTO &&
-                           (nc == 1 ? r_total <= (tb.M < 1024 ? kStreamMaxCandidates1 : kStreamMaxCandidatesWindows) ||
-                                          W < (uint64_t)kStreamBelowBudgets
-                                    : r_total <= kStreamMaxCandidatesN));
-    if (streamed) {
+    const bool tiles = tiles_take(L, tb.M);
+    const uint64_t stream_max = nc > 1 ? (tiles ? kTileMaxCandidatesN : kStreamMaxCandidatesN)
+                                : !tiles ? kStreamMaxCandidates1
+                                : tb.M < 1024 ? kTileMaxCandidates1
+                                              : kTileMaxCandidatesWindows;
+    const bool streamed =
+        schedule == ROTOR_SCHEDULE_DIAGONAL ||
+        (schedule == ROTOR_SCHEDULE_AUTO && (r_total <= stream_max || (nc == 1 && W < (uint64_t)kStreamBelowBudgets)));
+    if (streamed && tiles) {
         // one launch per tile-diagonal (rotor_tile.hip); the first fills the
         // leaves too
         const int groups = (L + kTileSide - 1) / kTileSide;
@@ -1956,7 +2050,7 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
                 return e;
             launch_tiles(level, stream, tb, w);
             uint64_t c1 = 0, c2 = 0, cells = 0;
-            for (int R = 0; R + level < groups; ++R)
+            for (int R = 0; obs && R + level < groups; ++R)
                 for (int s = R * kTileSide + 1; s <= min((R + 1) * kTileSide, L); ++s)
                     for (int t = max(s, (R + level) * kTileSide + 1); t <= min((R + level + 1) * kTileSide, L); ++t) {
                         c1 += (uint64_t)(t - s);
@@ -1974,15 +2068,24 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
                                                                  tb.dec, w);
     if ((e = launched(kLeaf, 0, 0, (uint64_t)L)) != hipSuccess)
         return e;
-    for (int d = 1; d < kT && d < L; ++d) {
+    for (int d = 1; d < (streamed ? L : kT) && d < L; ++d) {
         if ((e = before(kDiag)) != hipSuccess)
             return e;
-        diag_kernel<<<dim3(mb_diag, L - d, tb.n_chains), kEdgeThreads, 0, stream>>>(tb.params, L, tb.M, tb.pitch,
-                                                                                    tb.rows, d, tb.cost, tb.dec, w);
-        const uint64_t pairs = in_block_pairs(L, d);
+        if (streamed && d >= kSplitMinD)
+            diag_split_kernel<<<dim3(mb64, L - d, tb.n_chains), 256, 0, stream>>>(tb.params, L, tb.M, tb.pitch,
+                                                                                  tb.rows, d, tb.cost, tb.dec, w);
+        else if (streamed)
+            diag_kernel<kEdgeBudgets><<<dim3(mb_edge, L - d, tb.n_chains), kEdgeThreads, 0, stream>>>(
+                tb.params, L, tb.M, tb.pitch, tb.rows, d, 1, tb.cost, tb.dec, w);
+        else
+            diag_kernel<kDiagBudgets><<<dim3(mb_diag, L - d, tb.n_chains), kEdgeThreads, 0, stream>>>(
+                tb.params, L, tb.M, tb.pitch, tb.rows, d, 0, tb.cost, tb.dec, w);
+        const uint64_t pairs = streamed ? (uint64_t)(L - d) : in_block_pairs(L, d);
         if ((e = launched(kDiag, pairs * d, pairs, pairs)) != hipSuccess)
             return e;
     }
+    if (streamed)
+        return hipSuccess;
     const int nb = (L + kT - 1) / kT;
     // workgroups of the middle launches: few blocks cut the middle ranges
     // into runs for more workgroups (about 512), each of 32 splits or more

@@ -34,7 +34,7 @@ namespace rotor {
 namespace {
 
 constexpr int kG = kTileSide;
-constexpr int kTileMaxWaves = 16;
+constexpr int kTileMaxWaves = 8;
 // tile-diagonals from this one on have middle splits besides the rim
 constexpr int kInnerLevel = 3;
 
@@ -51,7 +51,6 @@ struct Key32 {
     typedef uint32_t K;
     static constexpr int kPer = 2;  // splits relaxed together (one three-way minimum per pair)
     static constexpr bool kAhead = true;  // operands of the next step held in registers
-    static constexpr bool kRimAhead = true;  // and of both halves of a tile's rim
     __device__ static K far() { return kInf32; }
     __device__ static K add(uint64_t prefix, int off, bool ok, int S)
     {
@@ -81,7 +80,6 @@ struct Key64 {
     typedef double K;
     static constexpr int kPer = 1;
     static constexpr bool kAhead = true;
-    static constexpr bool kRimAhead = false;
     __device__ static K far() { return __builtin_inf(); }
     __device__ static K add(uint64_t prefix, int off, bool ok, int)
     {
@@ -107,12 +105,20 @@ struct Key64 {
     }
 };
 
-// The budgets one pass of a workgroup fills: W from w0 on, 64 per wave.
+// Budgets of one pass over a tile: W from w0 on, 64 per wave, stored from
+// `from` on.  A tile of more budgets is filled by workgroups of overlapping
+// windows, W - halo apart: a row's cells at budget m need the rows below at no
+// less than m - reach (tile_reach), so a window whose rows reach no further
+// than halo finds what it stores in itself, computing its first halo budgets a
+// second time, and waits for no other.  Where the rows reach
+// further, the first workgroup walks all windows upwards (w0 a multiple of W)
+// and reads the lower ones back from the tables.
 struct Window {
-    int W, w0;
-    int at;  // this lane's place in the window
-    int m;   // its budget, w0 + at
-    int mc;  // the budget it loads, at most M
+    int W, halo, w0, from;
+    bool back;  // what lies below w0 is read back
+    int at;     // this lane's place in the window
+    int m;      // its budget, w0 + at
+    int mc;     // the budget it loads, at most M
 };
 
 // Fold in the stored() form of a result over any other splits.
@@ -160,7 +166,7 @@ __device__ __forceinline__ RowCells<P> read_row(const RowCells<P> *buf, const Wi
 {
     const int idx = wn.at - w;
     RowCells<P> c = buf[max(idx, 0)];
-    if (wn.w0 > 0 && idx < 0) {
+    if (wn.back && idx < 0) {
 #pragma unroll
         for (int j = 0; j < kG; ++j) {
             const int64_t o = (row + min(j, last)) * pitch;
@@ -459,6 +465,25 @@ __device__ __forceinline__ uint64_t lane_of64(int64_t v, int l)
            (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), l) << 32;
 }
 
+// The largest sum of shifts from a row of the tile down through it: low
+// splits shift by w_a of the stage before the lower row, C_2 by the row's own
+// w_abar.  v32 as in tile_finish.
+__device__ __forceinline__ int tile_reach(int32_t v32)
+{
+    int reach[kG];
+    reach[kG - 1] = 0;
+    int most = 0;
+#pragma unroll
+    for (int i = kG - 2; i >= 0; --i) {
+        reach[i] = lane_of(v32, 36 + i) + reach[i + 1];
+#pragma unroll
+        for (int e = i + 1; e < kG; ++e)
+            reach[i] = max(reach[i], lane_of(v32, 32 + e) + reach[e]);
+        most = max(most, reach[i]);
+    }
+    return most;
+}
+
 // Whether every cell of the tile is saturated at every budget from `base` on
 // (G(s, t) falls as s grows, so the tile's first row has the largest).
 __device__ inline bool tile_saturated(const ChainRows &r, const ChainWork &cw, int L, int s0, int t0, int base)
@@ -475,6 +500,25 @@ __device__ inline bool tile_saturated(const ChainRows &r, const ChainWork &cw, i
     return pos && base >= g;
 }
 
+// Inner results at the budgets that a second window computes again (the first
+// halo of every window but the first) are kept twice: in the cost slots, which
+// the window that stores those cells overwrites, and for the three lower rows
+// in the workspace's 2-byte section, which this order has no other use for: 128
+// half_pitch bytes per tile, half of them for each parity of its
+// tile-diagonal.  Budgets come in waves of 64.
+__device__ inline int halo_place(int base, int W, int halo)
+{
+    const int per = (W - halo) >> 6, own = halo >> 6;
+    const int q = base >> 6, v = q / per, x = q - v * per;
+    return v > 0 && x < own ? ((v - 1) * own + x) * 64 : -1;
+}
+__device__ inline int64_t *halo_of(const ChainWork &cw, int R, int level)
+{
+    // 12 rows of halo_pitch_of words: room for halos of up to 2/3 of W - halo
+    return (int64_t *)(cw.half + (int64_t)R * (64 * cw.hpitch)) + (level & 1) * (8 * cw.hpitch);
+}
+__device__ inline int64_t halo_pitch_of(const ChainWork &cw) { return cw.hpitch * 2 / 3 / 64 * 64; }
+
 // The inner middle splits [ka, kb] of tile (R, C) at the budgets of a
 // workgroup, left in the cost slots of its cells in the path's stored() form.
 // Waves hold 64 budgets each; n_kw waves of the same budgets take a part of
@@ -482,7 +526,7 @@ __device__ inline bool tile_saturated(const ChainRows &r, const ChainWork &cw, i
 template <class Key>
 __device__ __forceinline__ void tile_inner(const ChainRows &r, const ChainWork &cw, int L, int M, int64_t pitch, int R,
                                            int C, int S, int m, int at, int W, int n_kw, int kw, int64_t *tab,
-                                           char *lds)
+                                           int64_t *halo, int64_t halo_pitch, int W_T, int halo_T, char *lds)
 {
     typedef typename Key::P P;
     typedef typename P::Acc Acc;
@@ -526,27 +570,36 @@ __device__ __forceinline__ void tile_inner(const ChainRows &r, const ChainWork &
         __syncthreads();
     }
     if (kw == 0 && works && m <= M) {
+        // a copy for the window that computes these budgets a second time,
+        // whose cells may be final before it reads them
+        int64_t *copy = halo;
+        if (copy) {
+            const int x = halo_place(m - at % 64, W_T, halo_T);
+            copy = x >= 0 ? copy + x + at % 64 : nullptr;
+        }
 #pragma unroll
         for (int i = 0; i < kG; ++i) {
             const int64_t row = row_of(L, s0 + i, t0);
 #pragma unroll
-            for (int j = 0; j < kG; ++j)
+            for (int j = 0; j < kG; ++j) {
+                const int64_t v = n_kw > 1 ? (int64_t)part[(i * kG + j) * W] : P::stored(acc[i][j]);
                 if (j <= last)
-                    tab[(row + j) * pitch + m] =
-                        n_kw > 1 ? (int64_t)part[(i * kG + j) * W] : P::stored(acc[i][j]);
+                    tab[(row + j) * pitch + m] = v;
+                if (i > 0 && copy)
+                    copy[((i - 1) * kG + j) * halo_pitch] = v;
+            }
         }
     }
 }
 
 // One window of tile (R, C), C > R: the splits of its cells that tile_inner
-// did not take, C_2, the gates, the final cells.  Bound by latency and by the
-// instructions of one wave: the scalars of the tile come in two vector loads,
-// the operands in two batches, and the rows go through one loop body, in
-// which the row at hand is always the lowest of acc (a body per row would
-// miss the instruction cache and spill scalars).  INNER: tile_inner has left
-// its results in the cells' cost slots.
+// did not take, C_2, the gates, the final cells.  Bound by latency and, from
+// about five waves in a workgroup on, by instruction issue: the scalars of the
+// tile come in two vector loads, then the operands in two batches.  INNER:
+// tile_inner has left its results.  Returns whether the rows reach further
+// than a halo.
 template <class Key, bool INNER>
-__device__ __forceinline__ void tile_finish(const ChainRows &r, const ChainWork &cw, int L, int M, int64_t pitch,
+__device__ __forceinline__ bool tile_finish(const ChainRows &r, const ChainWork &cw, int L, int M, int64_t pitch,
                                             int R, int C, int S, const Window &wn, int64_t *tab, int16_t *dtab,
                                             char *lds)
 {
@@ -589,8 +642,16 @@ __device__ __forceinline__ void tile_finish(const ChainRows &r, const ChainWork 
     }
     RowCells<P> *const bufs = (RowCells<P> *)lds;
     const int base = __builtin_amdgcn_readfirstlane(m);
-    if (base > M || tile_saturated(r, cw, L, s0, t0, base)) {
-        // waves past M, and waves whose cells are all saturated
+    const TileRows<P> tr(tab, cw, L, pitch, s0, t0, mc);
+    const TileRim<Key> rim(s0 + kG - 1, t0 - 1);
+    const const_i64 pre = (const_i64)cw.pre;
+    // waves past M, and waves whose cells are all saturated, relax nothing
+    const bool sat = base > M || tile_saturated(r, cw, L, s0, t0, base);
+    // a window of its own whose rows reach below it stores nothing: the tile's
+    // first workgroup fills those budgets
+    const bool far = tile_reach(v32) > wn.halo;
+    const bool in = m <= M && m >= wn.from && (wn.w0 == 0 || wn.back || !far);
+    if (sat) {
 #pragma unroll 1
         for (int i = kG - 1;; --i) {
             RowStores st(tab, dtab, cw, row_of(L, s0 + i, t0), pitch);
@@ -599,72 +660,74 @@ __device__ __forceinline__ void tile_finish(const ChainRows &r, const ChainWork 
             for (int j = 0; j < kG; ++j) {
                 const FinalCell<P> f((Raw)(lane_of64(v64, 16 + j) - lane_of64(v64, 12 + i)), 0);
                 c.v[j] = f.v;
-                if (j <= last && m <= M)
+                if (j <= last && in)
                     st.store(f, m);
                 st.next();
             }
             if (i == 0)
-                return;
+                return far;
             bufs[(i & 1) * wn.W + wn.at] = c;
             lds_barrier();
         }
     }
-    const TileRows<P> tr(tab, cw, L, pitch, s0, t0, mc);
     Acc acc[kG][kG];
-    // operands: Y of the high splits, C_2's of the row at hand, X of the row
-    // at hand as Y of the three rows above (split k = s - 1)
-    Raw yh[kG][kG], xl[kG];
+    // operands: X of row i as Y of the rows u above (split k = s0 + i - 1), Y of
+    // the high splits, C_2's of the row at hand
+    Raw xl[kG][kG], yh[kG][kG];
     RowCells<P> c2;
-    const char *xrow = tr.base + row_of(L, s0 + kG - 2, s0 + kG - 2) * tr.rb;  // X (s - 1, s - 1) of the lowest row s
     {
+        typename TileRim<Key>::Half a, b;
         TileKeys<Key> keys;
         keys.clear();
-        const TileRim<Key> rim(s0 + kG - 1, t0 - 1);
-        const const_i64 pre = (const_i64)cw.pre;
-        typename TileRim<Key>::Half a, b;
         rim.template load<0>(a, r, tr);
-        if constexpr (Key::kRimAhead)
-            rim.template load<1>(b, r, tr);
+        const char *x = tr.base + row_of(L, s0, s0) * tr.rb;  // (s0 + u, s0 + u)
+#pragma unroll
+        for (int u = 0; u + 1 < kG; ++u) {
+#pragma unroll
+            for (int i = u + 1; i < kG; ++i)
+                xl[u][i] = P::load_off(x + (int64_t)(i - u - 1) * tr.rb, tr.mb);
+            x += (int64_t)(L - s0 - u + 1) * tr.rb;
+        }
+        const char *y = tr.base + row_of(L, t0 + 1, t0 + 1) * tr.rb;  // (t0 + e + 1, t0 + e + 1)
+#pragma unroll
+        for (int e = 0; e + 1 < kG; ++e) {
+            const uint32_t off = shifted_off<P::kBytes>(tr.mb, lane_of(v32, 40 + e));
+#pragma unroll
+            for (int j = e + 1; j < kG; ++j)
+                yh[e][j] = P::load_off(e < last ? y + (int64_t)(min(j, last) - e - 1) * tr.rb : tr.base, off);
+            y += (int64_t)(L - t0 - e) * tr.rb;
+        }
+        const char *p = tr.base + row_of(L, s0 + kG, t0) * tr.rb;
+        const uint32_t off = shifted_off<P::kBytes>(tr.mb, lane_of(v32, 39));
+#pragma unroll
+        for (int j = 0; j < kG; ++j)
+            c2.v[j] = P::load_off(p + tr.yd[j], off);
         rim.template relax<0>(keys, a, pre, S, mc);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (!Key::kRimAhead)
-            rim.template load<1>(b, r, tr);
+        rim.template load<1>(b, r, tr);
         [[maybe_unused]] int64_t inner[kG][kG];
         auto load_inner = [&]() {
+            const int at = base < wn.from ? halo_place(base, wn.W, wn.halo) : -1;
+            const int64_t hp = halo_pitch_of(cw);
 #pragma unroll
             for (int i = 0; i < kG; ++i) {
-                const int64_t *p = tab + row_of(L, s0 + i, t0) * pitch;
+                // the first row of a halo is not needed
+                const bool copy = i > 0 && at >= 0;
+                const int64_t *q = copy ? halo_of(cw, R, C - R) + (i - 1) * kG * hp + at
+                                        : tab + row_of(L, s0 + i, t0) * pitch + base;
+                const int64_t step = copy ? hp : pitch;
 #pragma unroll
                 for (int j = 0; j < kG; ++j) {
-                    inner[i][j] = load64(p, mc);
-                    p += j < last ? pitch : 0;
+                    inner[i][j] = load64(q, mc - base);
+                    q += j < last ? step : 0;
                 }
             }
         };
-        if constexpr (INNER && Key::kRimAhead)
+        if constexpr (INNER && P::kBytes == 4)
             load_inner();
-        {
-            const char *y = tr.base + row_of(L, t0 + 1, t0 + 1) * tr.rb;  // (t0 + e + 1, t0 + j)
-#pragma unroll
-            for (int e = 0; e + 1 < kG; ++e) {
-                const uint32_t off = shifted_off<P::kBytes>(tr.mb, lane_of(v32, 40 + e));
-#pragma unroll
-                for (int j = e + 1; j < kG; ++j)
-                    yh[e][j] = P::load_off(e < last ? y + (int64_t)(min(j, last) - e - 1) * tr.rb : tr.base, off);
-                y += (int64_t)(L - t0 - e) * tr.rb;
-            }
-            const char *p = tr.base + row_of(L, s0 + kG, t0) * tr.rb;
-            const uint32_t off = shifted_off<P::kBytes>(tr.mb, lane_of(v32, 39));
-#pragma unroll
-            for (int j = 0; j < kG; ++j)
-                c2.v[j] = P::load_off(p + tr.yd[j], off);
-#pragma unroll
-            for (int d = 1; d < kG; ++d)
-                xl[d] = P::load_off(xrow - (int64_t)((d - 1) * (L - s0 - kG + 3) + (d - 1) * (d - 2) / 2) * tr.rb, tr.mb);
-        }
         rim.template relax<1>(keys, b, pre, S, mc);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (INNER && !Key::kRimAhead)
+        if constexpr (INNER && P::kBytes == 8)  // fewer registers
             load_inner();
 #pragma unroll
         for (int i = 0; i < kG; ++i) {
@@ -677,11 +740,9 @@ __device__ __forceinline__ void tile_finish(const ChainRows &r, const ChainWork 
             }
         }
     }
-    const bool in = m <= M;
-    int i = kG - 1;
-#pragma unroll 1
-    for (;;) {
-        asm volatile("" : "+s"(i));  // one body for all rows
+#pragma unroll
+    for (int i = kG - 1; i >= 0; --i) {
+        __builtin_amdgcn_sched_barrier(0);
         const int s = s0 + i;
         const int64_t row = row_of(L, s, t0);
         const uint64_t pre_s = lane_of64(v64, i), ufub = lane_of64(v64, 8 + i);
@@ -690,7 +751,7 @@ __device__ __forceinline__ void tile_finish(const ChainRows &r, const ChainWork 
         int16_t d[kG];
 #pragma unroll
         for (int j = 0; j < kG; ++j) {
-            Acc a = acc[kG - 1][j];
+            Acc a = acc[i][j];
 #pragma unroll
             for (int e = 0; e < j; ++e)
                 P::relax(a, xh[e], P::yop(yh[e][j]), (uint32_t)(t0 + e + 1));
@@ -701,9 +762,15 @@ __device__ __forceinline__ void tile_finish(const ChainRows &r, const ChainWork 
                 xh[j] = P::xop(f.v, lane_of64(v64, 4 + j) - pre_s, (uint32_t)(t0 + j + 1), mc >= lane_of(v32, 40 + j));
         }
         RowCells<P> *const buf = bufs + (i & 1) * wn.W;
+        RowCells<P> v;
+        int w = 0;
         if (i > 0) {
             buf[wn.at] = c;
             lds_barrier();
+            // this row as Y of the rows above, and as C_2's operand of the next
+            w = lane_of(v32, 32 + i);
+            v = read_row<P>(buf, wn, w, tab, cw.shadow, row, last, pitch);
+            c2 = read_row<P>(buf, wn, lane_of(v32, 35 + i), tab, cw.shadow, row, last, pitch);
         }
         if (in) {
             RowStores st(tab, dtab, cw, row, pitch);
@@ -714,30 +781,15 @@ __device__ __forceinline__ void tile_finish(const ChainRows &r, const ChainWork 
                 st.next();
             }
         }
-        if (i == 0)
-            break;
-        // this row as Y of the rows above, and as C_2's operand of the next;
-        // rows above the tile's first get what is never used
-        const int w = lane_of(v32, 32 + i);
-        const RowCells<P> v = read_row<P>(buf, wn, w, tab, cw.shadow, row, last, pitch);
-        c2 = read_row<P>(buf, wn, lane_of(v32, 35 + i), tab, cw.shadow, row, last, pitch);
 #pragma unroll
-        for (int u = 1; u < kG; ++u) {
-            const typename P::X x = P::xop(xl[u], pre_s - lane_of64(v64, max(i - u, 0)), (uint32_t)s, mc >= w);
+        for (int u = 0; u < i; ++u) {
+            const typename P::X x = P::xop(xl[u][i], pre_s - lane_of64(v64, u), (uint32_t)s, mc >= w);
 #pragma unroll
-            for (int j = 0; j < kG; ++j) {
-                acc[kG - u][j] = acc[kG - 1 - u][j];
-                relax_earlier<P>(acc[kG - u][j], x, P::yop(v.v[j]), (uint32_t)s);
-            }
-        }
-        --i;
-        // X (s - u, s - 1) of the new row s (rows above the tile's first: the first)
-        if (i > 0) {
-#pragma unroll
-            for (int u = 1; u < kG; ++u)
-                xl[u] = P::load_off(tr.base + row_of(L, s0 + max(i - u, 0), s0 + i - 1) * tr.rb, tr.mb);
+            for (int j = 0; j < kG; ++j)
+                relax_earlier<P>(acc[u][j], x, P::yop(v.v[j]), (uint32_t)s);
         }
     }
+    return far;
 }
 
 // The diagonal tile R: stages s0 .. s0 + last, leaves included (Eq.
@@ -798,24 +850,35 @@ __device__ __forceinline__ void triangle_body(const ChainRows &r, const ChainWor
     }
 }
 
-// Calls body(window, R) for every window of the budgets, upwards: a later one
-// reads the cells of the earlier ones back.  R is opaque in each pass, or the
+// The passes of workgroup `v` of a tile, n_v of them sharing its windows, as
+// Window describes; body(window, R) fills one and returns whether the rows
+// reach too far for windows of their own.  R is opaque in each pass, or the
 // compiler computes every row address of the tile before the loop and spills
 // them.
 template <class F>
-__device__ __forceinline__ void for_windows(int M, int W, int R, F &&body)
+__device__ __forceinline__ void for_windows(int M, int W, int halo, int v, int n_v, int at, int R, F &&body)
 {
     Window wn;
     wn.W = W;
-    wn.at = threadIdx.x;
-    for (wn.w0 = 0; wn.w0 <= M; wn.w0 += W) {
-        if (wn.w0 > 0)
-            __syncthreads();
+    wn.at = at;
+    wn.back = false;
+    wn.halo = halo;
+    wn.w0 = v * (W - halo);
+    wn.from = v > 0 ? wn.w0 + halo : 0;
+    for (;;) {
         wn.m = wn.w0 + wn.at;
         wn.mc = min(wn.m, M);
         int tile = R;
         asm volatile("" : "+s"(tile));
-        body(wn, tile);
+        const bool far = body(wn, tile) || n_v == 1;
+        if (v > 0 || !far)
+            return;
+        wn.w0 += W;
+        if (wn.w0 > M)
+            return;
+        wn.from = wn.w0;
+        wn.back = true;
+        __syncthreads();  // the cells below are read back, the LDS rows written again
     }
 }
 
@@ -831,11 +894,12 @@ __global__ __launch_bounds__(kTileMaxWaves * 64) void triangle_kernel(const int6
     const ChainWork cw = chain_work(w, L, rows, pitch, c);
     int64_t *tab = cost + (int64_t)c * rows * pitch;
     int16_t *dtab = dec + (int64_t)c * rows * pitch;
-    for_windows(M, blockDim.x, R, [&](const Window &wn, int tile) {
+    for_windows(M, blockDim.x, 0, 0, 1, threadIdx.x, R, [&](const Window &wn, int tile) {
         if (cw.narrow(0))
             triangle_body<Narrow>(r, cw, L, M, pitch, tile, wn, tab, dtab, lds);
         else
             triangle_body<Wide>(r, cw, L, M, pitch, tile, wn, tab, dtab, lds);
+        return true;
     });
 }
 
@@ -853,13 +917,14 @@ __device__ __forceinline__ void with_key(const ChainWork &cw, int R, int C, F &&
 }
 
 // Tile-diagonal `level` of every chain, and the inner middle splits of the
-// next one, which read tile-diagonals up to level - 1 only: the first n_tiles
-// workgroups finish a tile each, the others take inner splits, so that the
-// products, most of the work, run beside the short dependent part.
+// next one, which read tile-diagonals up to level - 1 only: the first n_tiles *
+// n_v workgroups finish a window of a tile each, the others take inner splits, so that the products, most of the work, run beside
+// the short dependent part.
 template <bool INNER>
-__global__ __launch_bounds__(kTileMaxWaves * 64) void tile_kernel(const int64_t *__restrict__ params, int L, int M,
-                                                                  int64_t pitch, int64_t rows, int level, int n_kw,
-                                                                  int64_t *__restrict__ cost,
+__global__ __launch_bounds__(kTileMaxWaves * 64, 3) void tile_kernel(const int64_t *__restrict__ params, int L, int M,
+                                                                  int64_t pitch, int64_t rows, int level, int W, int overlap, int n_v,
+                                                                  int next_W, int next_overlap,
+                                                                  int n_kw, int64_t *__restrict__ cost,
                                                                   int16_t *__restrict__ dec, Work w)
 {
     extern __shared__ __align__(16) char lds[];
@@ -869,27 +934,60 @@ __global__ __launch_bounds__(kTileMaxWaves * 64) void tile_kernel(const int64_t 
     const ChainRows r = chain_rows(params, w, L, c);
     const ChainWork cw = chain_work(w, L, rows, pitch, c);
     int64_t *tab = cost + (int64_t)c * rows * pitch;
-    if ((int)blockIdx.x < n_tiles) {
-        const int R = blockIdx.x, C = R + level;
+    if ((int)blockIdx.x < n_tiles * n_v) {
+        const int v = blockIdx.x / n_tiles, R = blockIdx.x - v * n_tiles;
+        if ((int)threadIdx.x >= W)
+            return;
         int16_t *dtab = dec + (int64_t)c * rows * pitch;
-        with_key(cw, R, C, [&](auto key, int S) {
-            for_windows(M, blockDim.x, R, [&](const Window &wn, int tile) {
-                tile_finish<decltype(key), INNER>(r, cw, L, M, pitch, tile, tile + level, S, wn, tab, dtab, lds);
+        with_key(cw, R, R + level, [&](auto key, int S) {
+            for_windows(M, W, overlap, v, n_v, threadIdx.x, R, [&](const Window &wn, int tile) {
+                return tile_finish<decltype(key), INNER>(r, cw, L, M, pitch, tile, tile + level, S, wn, tab, dtab, lds);
             });
         });
     } else {
-        const int b = blockIdx.x - n_tiles;
+        const int b = blockIdx.x - n_tiles * n_v;
         const int R = b % (n_tiles - 1), chunk = b / (n_tiles - 1), C = R + level + 1;
-        const int W = blockDim.x / n_kw;
-        const int kw = __builtin_amdgcn_readfirstlane(threadIdx.x / W);
-        const int at = threadIdx.x - kw * W;
+        const int Wi = blockDim.x / n_kw;
+        const int kw = __builtin_amdgcn_readfirstlane(threadIdx.x / Wi);
+        const int at = threadIdx.x - kw * Wi;
+        int64_t *halo = next_W > 0 ? halo_of(cw, R, level + 1) : nullptr;
         with_key(cw, R, C, [&](auto key, int S) {
-            tile_inner<decltype(key)>(r, cw, L, M, pitch, R, C, S, chunk * W + at, at, W, n_kw, kw, tab, lds);
+            tile_inner<decltype(key)>(r, cw, L, M, pitch, R, C, S, chunk * Wi + at, at, Wi, n_kw, kw, tab, halo,
+                                      halo_pitch_of(cw), next_W, next_overlap, lds);
         });
     }
 }
 
 }  // namespace
+
+// Windows of a tile-diagonal of `tiles` tiles over all chains: W budgets of
+// one pass of a tile's workgroup, n_v workgroups per tile, `halo` budgets
+// apart from W.  Launches of few tiles take overlapping windows, small ones
+// where the budgets are few (sizes, and with them the halo needed, grow with
+// the budgets); from 128 tiles on the chip is full without them, and a
+// workgroup of four waves walks its tile's windows in turn (measured on
+// MI355X, against overlapping windows: ten chains of L = 101, M = 500 0.77 ->
+// 0.65 ms, 32 of L = 64, M = 640 0.81 -> 0.64 ms; one of L = 100, M = 1000, with
+// one workgroup of 16 waves per tile 0.49 -> 0.32 ms).
+struct TileWindows {
+    int W, halo, n_v;
+};
+static TileWindows tile_windows(const Tables &tb, int64_t tiles)
+{
+    const int chunks = (tb.M + 64) / 64;  // of 64 budgets
+    TileWindows tw;
+    if (tiles >= 128) {
+        const int passes = (chunks + 3) / 4;
+        tw.W = 64 * ((chunks + passes - 1) / passes);
+    } else {
+        tw.W = chunks <= 5 ? 64 * chunks : chunks < 12 ? 320 : 512;
+    }
+    tw.halo = tw.W == 320 ? 128 : 192;
+    // the workspace has a place for the halos' inner results from two blocks on
+    const bool overlap = tiles < 128 && tb.M >= tw.W && tb.L > kBlock;
+    tw.n_v = overlap ? (tb.M - tw.halo) / (tw.W - tw.halo) + 1 : 1;
+    return tw;
+}
 
 void launch_tiles(int level, hipStream_t stream, const Tables &tb, const Work &w)
 {
@@ -904,21 +1002,27 @@ void launch_tiles(int level, hipStream_t stream, const Tables &tb, const Work &w
         return;
     }
     const int n_inner = level + 1 >= kInnerLevel && n_tiles > 1 ? kG * (level + 1) - 3 * kG + 1 : 0;
-    int waves = min(chunks, kTileMaxWaves), n_kw = 1, inner_wgs = 0;
+    const TileWindows tw = tile_windows(tb, (int64_t)n_tiles * tb.n_chains);
+    // how the next launch reads the inner results this one leaves
+    const TileWindows next = tile_windows(tb, (int64_t)(n_tiles - 1) * tb.n_chains);
+    int waves = tw.W / 64, n_kw = 1, inner_wgs = 0;
     if (n_inner > 0) {
-        // waves of the inner splits: about 4096, at least 4 splits each
+        // waves of the inner splits: about 1024, at least 4 splits each (measured: 512
+        // and 2048 lose 5% at L = 339, M = 500 and ten chains of L = 101)
         const int64_t units = (int64_t)(n_tiles - 1) * chunks * tb.n_chains;
-        while (n_kw < kTileMaxWaves && units * n_kw < 4096 && n_inner >= 8 * n_kw)
+        while (n_kw < kTileMaxWaves && units * n_kw < 1024 && n_inner >= 8 * n_kw)
             n_kw *= 2;
         waves = (waves + n_kw - 1) / n_kw * n_kw;
         const int bw = waves / n_kw;
         inner_wgs = (chunks + bw - 1) / bw * (n_tiles - 1);
     }
     const int threads = 64 * waves;
-    const size_t lds = max(rows_lds * threads, n_kw > 1 ? kG * kG * sizeof(int64_t) * (size_t)(threads / n_kw) : 0);
-    (level >= kInnerLevel ? tile_kernel<true> : tile_kernel<false>)<<<dim3(n_tiles + inner_wgs, tb.n_chains), threads,
-                                                                      lds, stream>>>(
-        tb.params, tb.L, tb.M, tb.pitch, tb.rows, level, n_kw, tb.cost, tb.dec, w);
+    const size_t lds = max(rows_lds * tw.W,
+                           n_kw > 1 ? kG * kG * sizeof(int64_t) * (size_t)(threads / n_kw) : 0);
+    (level >= kInnerLevel ? tile_kernel<true> : tile_kernel<false>)<<<dim3(n_tiles * tw.n_v + inner_wgs, tb.n_chains),
+                                                                      threads, lds, stream>>>(
+        tb.params, tb.L, tb.M, tb.pitch, tb.rows, level, tw.W, tw.halo, tw.n_v, next.n_v > 1 ? next.W : 0,
+        next.halo, n_kw, tb.cost, tb.dec, w);
 }
 
 }  // namespace rotor

@@ -33,15 +33,29 @@ def test_tile_edges(L, M, shift):
     check(p, M)
 
 
-# windows of 1024 budgets: just one, a second of one budget, several; sizes up
-# to 700 reach past a whole window of a smaller workgroup, and 1500 past one of
-# 1024
-@pytest.mark.parametrize("scale", [1, 70, 150])
-@pytest.mark.parametrize("L,M", [(14, 1023), (14, 1024), (21, 1100), (10, 3100)])
+# windows of 320 and 512 budgets, their overlaps of 128 and 192 and budgets one
+# around their ends; sizes x 1 stay within the overlap, the larger ones reach
+# past it (the windows in turn) and past whole windows
+@pytest.mark.parametrize("scale", [1, 4, 30])
+@pytest.mark.parametrize("L,M", [(22, 319), (22, 320), (23, 448), (22, 511), (24, 575), (33, 703), (33, 704),
+                                 (45, 1023), (45, 1024), (50, 1151), (90, 2000)])
 def test_tile_windows(L, M, scale):
     p = chaingen.random_chains(1, L, seed=200 + L)
     p[:, 2:] *= scale
     check(p, M)
+
+
+# batches whose tile-diagonals go from windows in turn to overlapping ones as
+# they get fewer than 128 tiles
+@pytest.mark.parametrize("n,L,M", [(9, 75, 330), (20, 50, 600), (40, 21, 900)])
+def test_tile_windows_change(n, L, M):
+    check(chaingen.random_chains(n, L, seed=300 + L), M)
+
+
+# many budgets against few stages: diagonals instead of tiles
+@pytest.mark.parametrize("L,M", [(20, 480), (20, 481), (21, 512), (30, 800)])
+def test_diagonals_of_short_chains(L, M):
+    check(chaingen.random_chains(2, L, seed=400 + L), M)
 
 
 def test_inner_runs():
