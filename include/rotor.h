@@ -124,8 +124,8 @@ typedef struct {
 } rotor_op;
 
 /* Largest L accepted by rotor_solve (decisions are int16) and by
- * rotor_reconstruct (its walk keeps one 8-byte frame per pending sub-chain in
- * 64 KiB of LDS). */
+ * rotor_reconstruct (its walk keeps 16 bytes per stage in LDS, 128 KiB at
+ * that length). */
 #define ROTOR_MAX_L 32767
 #define ROTOR_MAX_L_RECONSTRUCT 8191
 #define ROTOR_MAX_CHAINS 65535
