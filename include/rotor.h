@@ -124,7 +124,7 @@ typedef struct {
 } rotor_op;
 
 /* Largest L accepted by rotor_solve (decisions are int16) and by
- * rotor_reconstruct (its walk keeps 16 bytes per stage in LDS, 128 KiB at
+ * rotor_reconstruct (its walk keeps 20 bytes per stage in LDS, 160 KiB at
  * that length). */
 #define ROTOR_MAX_L 32767
 #define ROTOR_MAX_L_RECONSTRUCT 8191

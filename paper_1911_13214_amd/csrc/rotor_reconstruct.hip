@@ -9,7 +9,7 @@
 // event); the other 32 do the same for a second frame.  A C_1 split reads both
 // its parts at once, so a walk waits once per C_1 split instead of once per
 // frame.  Measured on MI355X: ten budgets of a chain of L = 339, M = 500 (31 to
-// 66 C_1 splits and about 400 frames each) 231 -> 110 us.
+// 66 C_1 splits and about 400 frames each) 231 -> 99 us.
 // Pending items always cover disjoint stage ranges (a split leaves [s, s'-1]
 // pending while [s', t] is walked; the F_all^s of a run leave their B^s pending
 // while what follows the run is walked), so the stack never holds more than L
@@ -55,13 +55,14 @@ __global__ __launch_bounds__(64) void walk_kernel(const int64_t *__restrict__ pa
                                                   rotor_op *__restrict__ ops, int64_t *__restrict__ count,
                                                   int32_t *__restrict__ status)
 {
-    // two words per frame, then the prefix sums of w_abar (clamped to M + 1),
-    // modulo 2^32: a run's first budget below 0 shows exactly, since its sum
+    // two words per frame, then the prefix sums of w_abar and w_a (both clamped
+    // to M + 1), the sums modulo 2^32: a run's first budget below 0 shows exactly, since its sum
     // passes M < 2^28 by at most 2^28; later ones may wrap and are not read
     // outside [0, M]
     extern __shared__ __align__(8) uint64_t stack[];
     int32_t *const stack_hi = (int32_t *)(stack + L + 1);
     uint32_t *const kept = (uint32_t *)(stack_hi + L + 1);
+    int32_t *const wa_l = (int32_t *)(kept + L + 1);
     const int lane = threadIdx.x;
     const int b = blockIdx.x;
     const int64_t *wa = params + (int64_t)ROTOR_ROW_WA * L;
@@ -85,8 +86,10 @@ __global__ __launch_bounds__(64) void walk_kernel(const int64_t *__restrict__ pa
             const uint32_t up = __shfl_up(v, off);
             v += lane >= off ? up : 0u;
         }
-        if (l < L)
+        if (l < L) {
             kept[l + 1] = sum + v;
+            wa_l[l] = (int32_t)min(wa[l], (int64_t)M + 1);
+        }
         sum += __shfl(v, 63);
     }
     if (lane == 0)
@@ -170,14 +173,14 @@ __global__ __launch_bounds__(64) void walk_kernel(const int64_t *__restrict__ pa
                     st = ROTOR_ECORRUPT;
                     break;
                 }
-                const int64_t mr = m - wa[sp - 2];
+                const int mr = m - wa_l[sp - 2];
                 if (mr < 0 || mr > M || top + 1 > L) {
                     st = ROTOR_ECORRUPT;
                     break;
                 }
                 emit(sp - s, [&](int k) { return rotor_op{k == 0 ? ROTOR_F_CK : ROTOR_F_NONE, s + k}; });
                 Frame left{s, sp - 1, 0, 0, m, false};
-                f = Frame{sp, t, 0, 0, (int)mr, false};
+                f = Frame{sp, t, 0, 0, mr, false};
                 look(f, left);
                 push(stack, stack_hi, top++, left);
                 continue;
@@ -203,7 +206,7 @@ hipError_t launch_reconstruct(const int64_t *params, int L, int M, int64_t pitch
 {
     (void)rows;
     (void)hipGetLastError();  // an error the caller's earlier calls left behind is not this launch's
-    const size_t lds = (sizeof(uint64_t) + sizeof(int32_t) + sizeof(uint32_t)) * (size_t)(L + 1);
+    const size_t lds = (sizeof(uint64_t) + sizeof(int32_t) + sizeof(uint32_t) + sizeof(int32_t)) * (size_t)(L + 1);
     walk_kernel<<<dim3(n_budgets), 64, lds, stream>>>(params, L, M, pitch, dec_chain, budgets, cap, ops, count,
                                                       status);
     return hipGetLastError();
