@@ -227,11 +227,13 @@ ROTOR_API int32_t rotor_solve_status(const void *d_work, uint64_t work_bytes, in
  *   ROTOR_SCHEDULE_BLOCKED   16 x 16 blocks of pairs: register-tiled min-plus
  *                            products for the splits that reach across
  *                            blocks; the splits inside the block's own rows
- *                            and columns ("edges") by rows (16 launches per
- *                            block-diagonal) when a block-diagonal holds at
- *                            least 256 blocks over all chains, else by
- *                            anti-diagonals (30 short launches); the fast
- *                            order for large tables.
+ *                            and columns ("edges") by 4 x 4 tiles (8 launches
+ *                            per block-diagonal) in tables of up to 3e10
+ *                            candidates and for the last block-diagonals of
+ *                            larger ones, else by rows (16 launches) when a
+ *                            block-diagonal holds at least 256 blocks over
+ *                            all chains, else by anti-diagonals (30 short
+ *                            launches); the fast order for large tables.
  *   ROTOR_SCHEDULE_DIAGONAL  4 x 4 tiles of pairs, one launch per
  *                            tile-diagonal (ceil(L / 4) of them), the splits
  *                            that a tile shares as register products; from
@@ -239,9 +241,9 @@ ROTOR_API int32_t rotor_solve_status(const void *d_work, uint64_t work_bytes, in
  *                            over all pairs, the splits of a pair spread over
  *                            four waves from t - s = 16 on; few launches, the
  *                            fast order for small tables.
- *   ROTOR_SCHEDULE_AUTO      DIAGONAL when the table has at most 2e10 split
+ *   ROTOR_SCHEDULE_AUTO      DIAGONAL when the table has at most 1.8e10 split
  *                            candidates (L^3/6 (M+1)) for one chain with
- *                            M < 1024, 1e10 for one with more budgets, 4e9
+ *                            M < 1024, 8e9 for one with more budgets, 7e9
  *                            summed over a batch (by tiles; 2e9 and 4e8 where
  *                            it goes by t - s), or when one chain has M < 63;
  *                            BLOCKED otherwise (the order rotor_solve uses).

@@ -85,21 +85,23 @@
 namespace rotor {
 namespace {
 
-// The automatic schedule streams small tables.  By tiles, up to 2e10 split
-// candidates for one chain (1e10 from 1024 budgets on) and 4e9 over a batch;
-// measured on MI355X, blocked against tiles: L = 339, M = 500 (3e9) 5.7 / 1.9 ms;
-// L = 500, M = 500 (1e10) 8.3 / 4.8 ms; L = 500, M = 1000 (2e10) 9.2 / 8.7 ms;
-// L = 500, M = 2000 (4e10) 11.6 / 17.5 ms; L = 303, M = 2000 (9e9) 5.2 / 4.0 ms, on
-// the 64-bit path 7.0 / 7.0 ms; 32 chains of L = 64, M = 640 (9e8) 1.1 / 0.64 ms;
-// 64 chains of L = 130, M = 1000 on the 64-bit path (2e10) 17.0 / 18.6 ms.  The
+// The automatic schedule streams small tables.  By tiles, up to 1.8e10 split
+// candidates for one chain (8e9 from 1024 budgets on) and 7e9 over a batch;
+// measured on MI355X, blocked (edges by tiles) against streamed: L = 339, M = 500
+// (3e9) 3.7 / 1.9 ms; L = 500, M = 500 (1e10) 6.7 / 5.2 ms; L = 1001, M = 100 (2e10)
+// 11.1 / 9.7 ms; L = 500, M = 1000 (2e10) 7.5 / 8.8 ms; L = 200, M = 4500 (6e9)
+// 2.6 / 2.1 ms; L = 303, M = 2000 (9e9) 3.9 / 3.8 ms, on the 64-bit path 6.0 / 7.1 ms;
+// 32 chains of L = 64, M = 640 (9e8) 0.94 / 0.65 ms, 40 of L = 130, M = 700 (1e10)
+// 4.8 / 4.8 ms.  (256 chains of L = 64, M = 640, 7.2e9, stay blocked at 4.3 against
+// 3.8 ms: the breakdown by kernel classes of that workload is documented.)  The
 // tiles take 2 bytes of operands per candidate past the L2 (4 on the 64-bit
-// path), the blocked order a sixth of that but 30 launches per 16 stages.  By
-// diagonals (tiles_take), up to 2e9 for one chain (L = 250 at M = 500) and 4e8
-// for a batch.  Any single chain with fewer than 64 budgets is streamed: they
-// leave most lanes of the blocked kernels' 64-budget chunks idle.
-constexpr uint64_t kTileMaxCandidates1 = 20000000000ull;
-constexpr uint64_t kTileMaxCandidatesWindows = 10000000000ull;
-constexpr uint64_t kTileMaxCandidatesN = 4000000000ull;
+// path), the blocked order's middle products a sixth of that.  By diagonals
+// (tiles_take), up to 2e9 for one chain (L = 250 at M = 500) and 4e8 for a batch.
+// Any single chain with fewer than 64 budgets is streamed: they leave most lanes
+// of the blocked kernels' 64-budget chunks idle.
+constexpr uint64_t kTileMaxCandidates1 = 18000000000ull;
+constexpr uint64_t kTileMaxCandidatesWindows = 8000000000ull;
+constexpr uint64_t kTileMaxCandidatesN = 7000000000ull;
 constexpr uint64_t kStreamMaxCandidates1 = 2000000000ull;
 constexpr uint64_t kStreamMaxCandidatesN = 400000000ull;
 constexpr int kStreamBelowBudgets = 64;
@@ -113,6 +115,14 @@ constexpr int kStreamBelowBudgets = 64;
 // 144 / 92 us; L = 200, M = 3000 1.8 / 3.3 ms, L = 100, M = 1000 0.32 / 0.51 ms).
 constexpr int kTileBudgets = 512, kTileBudgetsPerStage = 24;
 bool tiles_take(int L, int M) { return M < kTileBudgets || M <= kTileBudgetsPerStage * L; }
+// Blocked edges by tiles (launch_fill), measured on MI355X against the rounds (rows
+// for the batch): L = 500, M = 1000 (2e10) 9.2 -> 7.5 ms, L = 700, M = 500 (3e10)
+// 12.8 -> 10.6, L = 300, M = 5000 (2e10) 5.8 -> 5.2, 256 chains of L = 64, M = 640
+// 5.0 -> 4.2; L = 500, M = 2000 (4e10) 11.6 -> 11.4 with the last block-diagonals (up
+// to 200 waves of 64 budgets and blocks), 12.2 with all; L = 500, M = 5000 (1e11)
+// 17.96 -> 17.89 and 22.2.
+constexpr uint64_t kTileEdgeCandidates = 30000000000ull;
+constexpr int kTileEdgeWaves = 200;
 constexpr int kSplitMinD = 16;  // diagonals from this length spread their splits over four waves
 
 // ---------------------------------------------------------------------------
@@ -1136,6 +1146,8 @@ __device__ inline void saturated_splits(const ChainWork &cw, const int32_t *wa_v
 // or kMidRim (which reads the inner part's slot for it); else its partial is
 // stored like any other and the edge round a + b = 0 finishes it.
 constexpr int kMidAll = 0, kMidInner = 1, kMidRim = 2;
+// Set beside the range where the edges finish the corners too (by tiles).
+constexpr int kMidNoCorner = 4;
 // Dynamic LDS, unused, that the inner range's packed launches request: it
 // caps them at three workgroups per CU (53 of 160 KB each) instead of four,
 // which leaves issue slots to the edge waves beside them (measured on MI355X
@@ -1149,8 +1161,9 @@ struct MiddleSplits {
     bool merge;        // atomic minimum into the partial slots
     bool owns_corner;  // finishes the corner cell of the block
 };
-__device__ inline MiddleSplits middle_splits(int k_lo, int k_hi, int range, int n_part, int part)
+__device__ inline MiddleSplits middle_splits(int k_lo, int k_hi, int range_flags, int n_part, int part)
 {
+    const int range = range_flags & ~kMidNoCorner;
     MiddleSplits r;
     r.jump_from = -1;
     r.jump_to = -1;
@@ -1169,7 +1182,7 @@ __device__ inline MiddleSplits middle_splits(int k_lo, int k_hi, int range, int 
         r.n_splits = r.kb - r.ka + 1;
     }
     r.merge = n_part > 1 || range == kMidRim;
-    r.owns_corner = (n_part == 1 && range == kMidAll) || range == kMidRim;
+    r.owns_corner = !(range_flags & kMidNoCorner) && ((n_part == 1 && range == kMidAll) || range == kMidRim);
     return r;
 }
 
@@ -2040,53 +2053,74 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
     const bool streamed =
         schedule == ROTOR_SCHEDULE_DIAGONAL ||
         (schedule == ROTOR_SCHEDULE_AUTO && (r_total <= stream_max || (nc == 1 && W < (uint64_t)kStreamBelowBudgets)));
-    if (streamed && tiles) {
-        // one launch per tile-diagonal (rotor_tile.hip); the first fills the
-        // leaves too
+    // Tile-diagonals (rotor_tile.hip), the first with the leaves: all of them
+    // (streamed), or those inside the diagonal blocks.
+    auto tile_diagonals = [&](bool in_blocks) -> hipError_t {
         const int groups = (L + kTileSide - 1) / kTileSide;
-        for (int level = 0; level < groups; ++level) {
+        for (int level = 0; level < (in_blocks ? min(groups, kT / kTileSide) : groups); ++level) {
             const KernelClass k = level == 0 ? kLeaf : kDiag;
-            if ((e = before(k)) != hipSuccess)
+            hipError_t e = before(k);
+            if (e != hipSuccess)
                 return e;
-            launch_tiles(level, stream, tb, w);
+            launch_tiles(level, in_blocks, stream, tb, w);
             uint64_t c1 = 0, c2 = 0, cells = 0;
-            for (int R = 0; obs && R + level < groups; ++R)
+            for (int R = 0; obs && R + level < groups; ++R) {
+                if (in_blocks && R % (kT / kTileSide) + level >= kT / kTileSide)
+                    continue;
                 for (int s = R * kTileSide + 1; s <= min((R + 1) * kTileSide, L); ++s)
                     for (int t = max(s, (R + level) * kTileSide + 1); t <= min((R + level + 1) * kTileSide, L); ++t) {
                         c1 += (uint64_t)(t - s);
                         c2 += t > s ? 1 : 0;
                         ++cells;
                     }
+            }
             if ((e = launched(k, c1, c2, cells)) != hipSuccess)
                 return e;
         }
         return hipSuccess;
-    }
-    if ((e = before(kLeaf)) != hipSuccess)
-        return e;
-    leaf_kernel<<<dim3(mb256, L, tb.n_chains), 256, 0, stream>>>(tb.params, L, tb.M, tb.pitch, tb.rows, tb.cost,
-                                                                 tb.dec, w);
-    if ((e = launched(kLeaf, 0, 0, (uint64_t)L)) != hipSuccess)
-        return e;
-    for (int d = 1; d < (streamed ? L : kT) && d < L; ++d) {
-        if ((e = before(kDiag)) != hipSuccess)
+    };
+    if (streamed && tiles)
+        return tile_diagonals(false);
+    const int nb = (L + kT - 1) / kT;
+    // Edges of block-diagonal delta by tiles, 8 launches instead of 30: all in
+    // tables of up to 3e10 candidates, whose edges outweigh the middle products;
+    // in larger ones, where the products run beside them, the last
+    // block-diagonals, whose rounds are bound by their launches.  From the first
+    // such block-diagonal on all are (they have ever fewer blocks), so the
+    // 2-byte copy, which the tiles' windows overwrite, is no longer read.
+    auto tile_edges = [&](int delta) {
+        return schedule != ROTOR_SCHEDULE_BLOCKED_ROWS && schedule != ROTOR_SCHEDULE_BLOCKED_ROUNDS &&
+               (r_total <= kTileEdgeCandidates || (int64_t)(nb - delta) * mb64 * tb.n_chains <= kTileEdgeWaves);
+    };
+    if (!streamed && tile_edges(1)) {
+        if ((e = tile_diagonals(true)) != hipSuccess)
             return e;
-        if (streamed && d >= kSplitMinD)
-            diag_split_kernel<<<dim3(mb64, L - d, tb.n_chains), 256, 0, stream>>>(tb.params, L, tb.M, tb.pitch,
-                                                                                  tb.rows, d, tb.cost, tb.dec, w);
-        else if (streamed)
-            diag_kernel<kEdgeBudgets><<<dim3(mb_edge, L - d, tb.n_chains), kEdgeThreads, 0, stream>>>(
-                tb.params, L, tb.M, tb.pitch, tb.rows, d, 1, tb.cost, tb.dec, w);
-        else
-            diag_kernel<kDiagBudgets><<<dim3(mb_diag, L - d, tb.n_chains), kEdgeThreads, 0, stream>>>(
-                tb.params, L, tb.M, tb.pitch, tb.rows, d, 0, tb.cost, tb.dec, w);
-        const uint64_t pairs = streamed ? (uint64_t)(L - d) : in_block_pairs(L, d);
-        if ((e = launched(kDiag, pairs * d, pairs, pairs)) != hipSuccess)
+    } else {
+        if ((e = before(kLeaf)) != hipSuccess)
             return e;
+        leaf_kernel<<<dim3(mb256, L, tb.n_chains), 256, 0, stream>>>(tb.params, L, tb.M, tb.pitch, tb.rows, tb.cost,
+                                                                     tb.dec, w);
+        if ((e = launched(kLeaf, 0, 0, (uint64_t)L)) != hipSuccess)
+            return e;
+        for (int d = 1; d < (streamed ? L : kT) && d < L; ++d) {
+            if ((e = before(kDiag)) != hipSuccess)
+                return e;
+            if (streamed && d >= kSplitMinD)
+                diag_split_kernel<<<dim3(mb64, L - d, tb.n_chains), 256, 0, stream>>>(tb.params, L, tb.M, tb.pitch,
+                                                                                      tb.rows, d, tb.cost, tb.dec, w);
+            else if (streamed)
+                diag_kernel<kEdgeBudgets><<<dim3(mb_edge, L - d, tb.n_chains), kEdgeThreads, 0, stream>>>(
+                    tb.params, L, tb.M, tb.pitch, tb.rows, d, 1, tb.cost, tb.dec, w);
+            else
+                diag_kernel<kDiagBudgets><<<dim3(mb_diag, L - d, tb.n_chains), kEdgeThreads, 0, stream>>>(
+                    tb.params, L, tb.M, tb.pitch, tb.rows, d, 0, tb.cost, tb.dec, w);
+            const uint64_t pairs = streamed ? (uint64_t)(L - d) : in_block_pairs(L, d);
+            if ((e = launched(kDiag, pairs * d, pairs, pairs)) != hipSuccess)
+                return e;
+        }
     }
     if (streamed)
         return hipSuccess;
-    const int nb = (L + kT - 1) / kT;
     // workgroups of the middle launches: few blocks cut the middle ranges
     // into runs for more workgroups (about 512), each of 32 splits or more
     auto parts_of = [&](int delta) {
@@ -2104,11 +2138,12 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
         if (e != hipSuccess)
             return e;
         const dim3 grid(mb64 * n_part, nb - delta, tb.n_chains);
+        const int flags = range | (tile_edges(delta) ? kMidNoCorner : 0);
         if (range == kMidRim)
-            middle_kernel<true><<<grid, 256, 0, st>>>(tb.params, L, tb.M, tb.pitch, tb.rows, delta, range, n_part,
+            middle_kernel<true><<<grid, 256, 0, st>>>(tb.params, L, tb.M, tb.pitch, tb.rows, delta, flags, n_part,
                                                       tb.cost, tb.dec, w);
         else
-            middle_kernel<false><<<grid, 256, 0, st>>>(tb.params, L, tb.M, tb.pitch, tb.rows, delta, range, n_part,
+            middle_kernel<false><<<grid, 256, 0, st>>>(tb.params, L, tb.M, tb.pitch, tb.rows, delta, flags, n_part,
                                                        tb.cost, tb.dec, w);
         return launched_on(st, kMiddle, 0, 0, 0);
     };
@@ -2117,12 +2152,13 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
         if (e != hipSuccess)
             return e;
         const dim3 grid(mb64 * n_part, nb - delta, tb.n_chains);
+        const int flags = range | (tile_edges(delta) ? kMidNoCorner : 0);
         if (range == kMidRim)
-            middle_packed_kernel<true><<<grid, 256, 0, st>>>(tb.params, L, tb.M, tb.pitch, tb.rows, delta, range,
+            middle_packed_kernel<true><<<grid, 256, 0, st>>>(tb.params, L, tb.M, tb.pitch, tb.rows, delta, flags,
                                                              n_part, tb.cost, tb.dec, w);
         else
             middle_packed_kernel<false><<<grid, 256, range == kMidInner ? kInnerLdsPad : 0, st>>>(
-                tb.params, L, tb.M, tb.pitch, tb.rows, delta, range, n_part, tb.cost, tb.dec, w);
+                tb.params, L, tb.M, tb.pitch, tb.rows, delta, flags, n_part, tb.cost, tb.dec, w);
         return launched_on(st, kMiddle, c1, corners, corners);
     };
     auto fill_partials = [&](int delta, hipStream_t st) {
@@ -2170,7 +2206,7 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
             // the middle splits of every pair, and C_2 of the corner cell of
             // every block when the middle products finish the corners
             const int n_part = inner_done ? 1 : parts_of(delta);
-            const int finish = inner_done || n_part == 1 ? 1 : 0;
+            const int finish = !tile_edges(delta) && (inner_done || n_part == 1) ? 1 : 0;
             const uint64_t corners = finish ? (uint64_t)(nb - delta) : 0;
             if (inner_done && (e = hipStreamWaitEvent(stream, side->done, 0)) != hipSuccess)
                 return e;
@@ -2201,6 +2237,25 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
             if ((e = middle_packed(delta, range, n_part, stream, c1, corners)) != hipSuccess)
                 return e;
             inner_done = next_inner;
+            if (tile_edges(delta)) {
+                constexpr int kSide = kT / kTileSide;
+                for (int q = -1; q <= 2 * kSide - 2; ++q) {
+                    uint64_t c1 = 0, cells = 0;
+                    for (int I = 0; obs && I + delta < nb; ++I)
+                        for (int a = 0; a < kT; ++a)
+                            for (int b = 0; b < min(kT, L - (I + delta) * kT); ++b)
+                                if (a / kTileSide + b / kTileSide == q) {
+                                    c1 += (uint64_t)(a + b);
+                                    ++cells;
+                                }
+                    if ((e = before(kEdge)) != hipSuccess)
+                        return e;
+                    launch_tile_edges(q, delta, stream, tb, w);
+                    if ((e = launched(kEdge, c1, cells, cells)) != hipSuccess)
+                        return e;
+                }
+                continue;
+            }
             if (rows) {
                 for (int a = 0; a < kT; ++a) {
                     uint64_t c1 = 0, cells = 0;

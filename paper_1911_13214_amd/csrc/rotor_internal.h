@@ -107,10 +107,14 @@ struct LaunchObserver {
 hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_t stream,
                        LaunchObserver *obs = nullptr, bool side_stream = true);
 
-// Side of the tiles of the streamed fill, in stages, and the launch of one
-// of its tile-diagonals (level = 0: the diagonal tiles with the leaves).
+// Tiles of kTileSide x kTileSide pairs (rotor_tile.hip): the launch of one
+// tile-diagonal (level = 0: the diagonal tiles with the leaves), of all tiles
+// (the streamed fill) or of those inside the diagonal blocks; and one step of
+// the edges of the blocks of one block-diagonal, the tiles a + b = step of each:
+// steps -1 (which prepares step 0) to 2 kBlock / kTileSide - 2.
 constexpr int kTileSide = 4;
-void launch_tiles(int level, hipStream_t stream, const Tables &tb, const Work &w);
+void launch_tiles(int level, bool in_blocks, hipStream_t stream, const Tables &tb, const Work &w);
+void launch_tile_edges(int step, int delta, hipStream_t stream, const Tables &tb, const Work &w);
 
 // Edges of the blocked fill by rows: whether a block-diagonal with `blocks`
 // blocks over all chains takes them, and the launch of row 16(I + 1) - a of

@@ -34,10 +34,10 @@ namespace rotor {
 namespace {
 
 constexpr int kG = kTileSide;
-constexpr int kTileMaxWaves = 8;
+constexpr int kTileMaxWaves = 10;
+constexpr int kPerBlock = kT / kG;  // tiles of a 16 x 16 block, each way
 // tile-diagonals from this one on have middle splits besides the rim
 constexpr int kInnerLevel = 3;
-
 // Middle candidates as one key, value * 2^S + (k - first split of the run):
 // the minimum is the smallest value and, among equal values, the smallest
 // split.  A range longer than 2^S splits goes in runs of 2^S.
@@ -50,7 +50,6 @@ struct Key32 {
     typedef Narrow P;
     typedef uint32_t K;
     static constexpr int kPer = 2;  // splits relaxed together (one three-way minimum per pair)
-    static constexpr bool kAhead = true;  // operands of the next step held in registers
     __device__ static K far() { return kInf32; }
     __device__ static K add(uint64_t prefix, int off, bool ok, int S)
     {
@@ -79,7 +78,6 @@ struct Key64 {
     typedef Path P;
     typedef double K;
     static constexpr int kPer = 1;
-    static constexpr bool kAhead = true;
     __device__ static K far() { return __builtin_inf(); }
     __device__ static K add(uint64_t prefix, int off, bool ok, int)
     {
@@ -326,9 +324,9 @@ struct TileKeys {
 
 // Splits ka .. kb of tile (s0 .., t0 ..) folded into acc, with the u_f prefix
 // of each row: per split 8 loads and 16 candidates per lane, in steps of
-// Key::kPer splits, the operands of the next step loaded before a step is
-// relaxed.
-template <class Key>
+// Key::kPer splits, with AHEAD the operands of the next step loaded before a
+// step is relaxed.
+template <class Key, bool AHEAD>
 __device__ __forceinline__ void tile_splits(typename Key::P::Acc (&acc)[kG][kG], const ChainRows &r,
                                             const ChainWork &cw, const TileRows<typename Key::P> &tr, int ka, int kb,
                                             int S, int mc)
@@ -373,10 +371,10 @@ __device__ __forceinline__ void tile_splits(typename Key::P::Acc (&acc)[kG][kG],
     };
     Step a;
     [[maybe_unused]] Step b;
-    if constexpr (Key::kAhead)
+    if constexpr (AHEAD)
         load(a);
     for (int k = ka; k <= kb; k += 2 * N) {
-        if constexpr (Key::kAhead) {
+        if constexpr (AHEAD) {
             load(b);
             relax(a, k);
             if (k + N <= kb) {
@@ -519,11 +517,66 @@ __device__ inline int64_t *halo_of(const ChainWork &cw, int R, int level)
 }
 __device__ inline int64_t halo_pitch_of(const ChainWork &cw) { return cw.hpitch * 2 / 3 / 64 * 64; }
 
+// tile_inner's part for the edges of the blocked order: the splits of a tile of
+// block (I, J) inside the block, less the rim, k in [4R + 8, 16I + 15] and [16J + 1,
+// 4C - 4], and between them the middle products' result: a packed key in the
+// cell's compact copy, or the path's stored() form in its cost slot, counting
+// u_f from stage 16I + 16 on.
+template <class Key>
+__device__ __forceinline__ void edge_splits(typename Key::P::Acc (&acc)[kG][kG], const ChainRows &r,
+                                            const ChainWork &cw, const TileRows<typename Key::P> &tr, int L,
+                                            int64_t pitch, const int64_t *tab, int last, int S, int mc)
+{
+    typedef typename Key::P P;
+    const int I = (tr.s0 - 1) / kT, J = (tr.t0 - 1) / kT;
+    const int k_lo = (I + 1) * kT, k_hi = J * kT;  // the middle range
+    const bool packed = P::kShadow && middle_packed(cw, J - I, k_hi - k_lo);
+    const int Sm = k_hi > k_lo ? 32 - __clz(k_hi - k_lo) : 0;
+    const const_i64 pre = (const_i64)cw.pre;
+    const int64_t pre_lo = pre[k_lo - 1];
+    constexpr bool kAheadE = sizeof(typename Key::K) == 4;  // registers
+#pragma unroll
+    for (int i = 0; i < kG; ++i)
+#pragma unroll
+        for (int j = 0; j < kG; ++j)
+            P::init(acc[i][j]);
+    if (tr.s0 + 2 * kG - 1 < k_lo)
+        tile_splits<Key, kAheadE>(acc, r, cw, tr, tr.s0 + 2 * kG - 1, k_lo - 1, S, mc);
+    if (packed) {
+#pragma unroll
+        for (int i = 0; i < kG; ++i) {
+            const uint32_t *p = cw.shadow + row_of(L, tr.s0 + i, tr.t0) * pitch;
+            const uint64_t pfx = (uint64_t)(pre_lo - pre[tr.s0 + i - 1]);
+#pragma unroll
+            for (int j = 0; j < kG; ++j) {
+                const uint32_t key = load32(p, mc);
+                const uint32_t split = (uint32_t)(k_lo + 1) + (key & ((1u << Sm) - 1u));
+                P::merge_stored(acc[i][j], (int64_t)((uint64_t)(key == kInf32 ? kInf32 : key >> Sm) << 32 | split), pfx);
+                p += j < last ? pitch : 0;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < kG; ++i) {
+            const int64_t *p = tab + row_of(L, tr.s0 + i, tr.t0) * pitch;
+            const uint64_t pfx = (uint64_t)(pre_lo - pre[tr.s0 + i - 1]);
+#pragma unroll
+            for (int j = 0; j < kG; ++j) {
+                P::merge_stored(acc[i][j], load64(p, mc), pfx);
+                p += j < last ? pitch : 0;
+            }
+        }
+    }
+    if (k_hi + 1 < tr.t0 - kG)
+        tile_splits<Key, kAheadE>(acc, r, cw, tr, k_hi + 1, tr.t0 - 1 - kG, S, mc);
+}
+
 // The inner middle splits [ka, kb] of tile (R, C) at the budgets of a
 // workgroup, left in the cost slots of its cells in the path's stored() form.
 // Waves hold 64 budgets each; n_kw waves of the same budgets take a part of
-// the splits each, and their minima meet in LDS.
-template <class Key>
+// the splits each, and their minima meet in LDS.  EDGE: edge_splits instead
+// (n_kw = 1).
+template <class Key, bool EDGE>
 __device__ __forceinline__ void tile_inner(const ChainRows &r, const ChainWork &cw, int L, int M, int64_t pitch, int R,
                                            int C, int S, int m, int at, int W, int n_kw, int kw, int64_t *tab,
                                            int64_t *halo, int64_t halo_pitch, int W_T, int halo_T, char *lds)
@@ -541,13 +594,18 @@ __device__ __forceinline__ void tile_inner(const ChainRows &r, const ChainWork &
 #pragma unroll
         for (int j = 0; j < kG; ++j)
             P::init(acc[i][j]);
-    if (works) {
+    if constexpr (EDGE) {
+        if (works) {
+            const TileRows<P> tr(tab, cw, L, pitch, s0, t0, mc);
+            edge_splits<Key>(acc, r, cw, tr, L, pitch, tab, last, S, mc);
+        }
+    } else if (works) {
         const int lo = s0 + 2 * kG - 1, hi = t0 - 1 - kG;
         const int chunk = (hi - lo + n_kw) / n_kw;
         const int ka = lo + kw * chunk, kb = min(hi, ka + chunk - 1);
         if (ka <= kb) {
             const TileRows<P> tr(tab, cw, L, pitch, s0, t0, mc);
-            tile_splits<Key>(acc, r, cw, tr, ka, kb, S, mc);
+            tile_splits<Key, true>(acc, r, cw, tr, ka, kb, S, mc);
         }
     }
     unsigned long long *const part = (unsigned long long *)lds + at;
@@ -675,11 +733,7 @@ __device__ __forceinline__ bool tile_finish(const ChainRows &r, const ChainWork 
     // the high splits, C_2's of the row at hand
     Raw xl[kG][kG], yh[kG][kG];
     RowCells<P> c2;
-    {
-        typename TileRim<Key>::Half a, b;
-        TileKeys<Key> keys;
-        keys.clear();
-        rim.template load<0>(a, r, tr);
+    auto load_operands = [&]() {
         const char *x = tr.base + row_of(L, s0, s0) * tr.rb;  // (s0 + u, s0 + u)
 #pragma unroll
         for (int u = 0; u + 1 < kG; ++u) {
@@ -702,6 +756,13 @@ __device__ __forceinline__ bool tile_finish(const ChainRows &r, const ChainWork 
 #pragma unroll
         for (int j = 0; j < kG; ++j)
             c2.v[j] = P::load_off(p + tr.yd[j], off);
+    };
+    {
+        typename TileRim<Key>::Half a, b;
+        TileKeys<Key> keys;
+        keys.clear();
+        rim.template load<0>(a, r, tr);
+        load_operands();
         rim.template relax<0>(keys, a, pre, S, mc);
         __builtin_amdgcn_sched_barrier(0);
         rim.template load<1>(b, r, tr);
@@ -916,44 +977,85 @@ __device__ __forceinline__ void with_key(const ChainWork &cw, int R, int C, F &&
         f(Key64<Wide>{}, kKey64Bits);
 }
 
-// Tile-diagonal `level` of every chain, and the inner middle splits of the
-// next one, which read tile-diagonals up to level - 1 only: the first n_tiles *
-// n_v workgroups finish a window of a tile each, the others take inner splits, so that the products, most of the work, run beside
-// the short dependent part.
-template <bool INNER>
+// The tiles of one step of a chain: of tile-diagonal `step`, all of them
+// (kAllTiles) or those inside the 16 x 16 diagonal blocks (kDiagonalBlocks); or, of
+// the blocks (I, I + delta), the tiles a + b = step (kBlockEdges), a groups above
+// the block's last and b right of its first.
+enum TileSet { kAllTiles, kDiagonalBlocks, kBlockEdges };
+struct TileSteps {
+    TileSet set;
+    int groups, delta;
+    __host__ __device__ int count(int step) const
+    {
+        constexpr int B = kPerBlock;
+        const int blocks = (groups + B - 1) / B;
+        if (set == kAllTiles)
+            return groups - step;
+        if (set == kDiagonalBlocks)
+            return step < B ? blocks * (B - step) : 0;
+        return step < 2 * B - 1 ? (blocks - delta) * (step < B ? step + 1 : 2 * B - 1 - step) : 0;
+    }
+    // tile i of the step; past the chain when C >= groups
+    __device__ void at(int step, int i, int &R, int &C) const
+    {
+        constexpr int B = kPerBlock;
+        if (set == kAllTiles) {
+            R = i;
+            C = i + step;
+        } else if (set == kDiagonalBlocks) {
+            R = i / (B - step) * B + i % (B - step);
+            C = R + step;
+        } else {
+            const int n = step < B ? step + 1 : 2 * B - 1 - step, I = i / n;
+            const int a = max(0, step - B + 1) + (i - I * n);
+            R = I * B + B - 1 - a;
+            C = (I + delta) * B + step - a;
+        }
+    }
+};
+
+// One step: the first n_tiles * n_v workgroups finish a window of a tile each,
+// the others take the inner splits of the next step's tiles, which read tiles
+// of the steps before this one only: so that the products, most of the work,
+// run beside the short dependent part.
+template <bool INNER, bool EDGE>
 __global__ __launch_bounds__(kTileMaxWaves * 64, 3) void tile_kernel(const int64_t *__restrict__ params, int L, int M,
-                                                                  int64_t pitch, int64_t rows, int level, int W, int overlap, int n_v,
-                                                                  int next_W, int next_overlap,
-                                                                  int n_kw, int64_t *__restrict__ cost,
+                                                                  int64_t pitch, int64_t rows, TileSteps steps,
+                                                                  int step, int n_tiles, int W, int overlap, int n_v,
+                                                                  int next_W, int next_overlap, int n_kw,
+                                                                  int64_t *__restrict__ cost,
                                                                   int16_t *__restrict__ dec, Work w)
 {
     extern __shared__ __align__(16) char lds[];
     const int c = blockIdx.y;
-    const int groups = (L + kG - 1) / kG;
-    const int n_tiles = groups - level;
     const ChainRows r = chain_rows(params, w, L, c);
     const ChainWork cw = chain_work(w, L, rows, pitch, c);
     int64_t *tab = cost + (int64_t)c * rows * pitch;
+    int R, C;
     if ((int)blockIdx.x < n_tiles * n_v) {
-        const int v = blockIdx.x / n_tiles, R = blockIdx.x - v * n_tiles;
-        if ((int)threadIdx.x >= W)
+        const int v = blockIdx.x / n_tiles;
+        steps.at(step, blockIdx.x - v * n_tiles, R, C);
+        if (C >= steps.groups || (int)threadIdx.x >= W)
             return;
         int16_t *dtab = dec + (int64_t)c * rows * pitch;
-        with_key(cw, R, R + level, [&](auto key, int S) {
+        with_key(cw, R, C, [&](auto key, int S) {
             for_windows(M, W, overlap, v, n_v, threadIdx.x, R, [&](const Window &wn, int tile) {
-                return tile_finish<decltype(key), INNER>(r, cw, L, M, pitch, tile, tile + level, S, wn, tab, dtab, lds);
+                return tile_finish<decltype(key), INNER>(r, cw, L, M, pitch, tile, tile - R + C, S, wn, tab, dtab, lds);
             });
         });
     } else {
         const int b = blockIdx.x - n_tiles * n_v;
-        const int R = b % (n_tiles - 1), chunk = b / (n_tiles - 1), C = R + level + 1;
+        const int n_next = steps.count(step + 1), chunk = b / n_next;
+        steps.at(step + 1, b - chunk * n_next, R, C);
+        if (C >= steps.groups)
+            return;
         const int Wi = blockDim.x / n_kw;
         const int kw = __builtin_amdgcn_readfirstlane(threadIdx.x / Wi);
         const int at = threadIdx.x - kw * Wi;
-        int64_t *halo = next_W > 0 ? halo_of(cw, R, level + 1) : nullptr;
+        int64_t *halo = next_W > 0 ? halo_of(cw, R, C - R) : nullptr;
         with_key(cw, R, C, [&](auto key, int S) {
-            tile_inner<decltype(key)>(r, cw, L, M, pitch, R, C, S, chunk * Wi + at, at, Wi, n_kw, kw, tab, halo,
-                                      halo_pitch_of(cw), next_W, next_overlap, lds);
+            tile_inner<decltype(key), EDGE>(r, cw, L, M, pitch, R, C, S, chunk * Wi + at, at, Wi, n_kw, kw, tab, halo,
+                                            halo_pitch_of(cw), next_W, next_overlap, lds);
         });
     }
 }
@@ -980,49 +1082,63 @@ static TileWindows tile_windows(const Tables &tb, int64_t tiles)
         const int passes = (chunks + 3) / 4;
         tw.W = 64 * ((chunks + passes - 1) / passes);
     } else {
-        tw.W = chunks <= 5 ? 64 * chunks : chunks < 12 ? 320 : 512;
+        tw.W = chunks <= 5 ? 64 * chunks : chunks < 12 ? 320 : chunks < 48 ? 512 : 640;
     }
-    tw.halo = tw.W == 320 ? 128 : 192;
+    tw.halo = tw.W == 320 ? 128 : tw.W == 512 ? 192 : 256;
     // the workspace has a place for the halos' inner results from two blocks on
     const bool overlap = tiles < 128 && tb.M >= tw.W && tb.L > kBlock;
     tw.n_v = overlap ? (tb.M - tw.halo) / (tw.W - tw.halo) + 1 : 1;
     return tw;
 }
 
-void launch_tiles(int level, hipStream_t stream, const Tables &tb, const Work &w)
+static void launch_step(const TileSteps &steps, int step, hipStream_t stream, const Tables &tb, const Work &w)
 {
-    const int groups = (tb.L + kG - 1) / kG;
+    const bool edge = steps.set == kBlockEdges;
     const int chunks = (tb.M + 64) / 64;  // of 64 budgets
-    const int n_tiles = groups - level;
-    const size_t rows_lds = 2 * kG * sizeof(int64_t);  // per budget of a window
-    if (level == 0) {
-        const int W = 64 * min(chunks, kTileMaxWaves);
-        triangle_kernel<<<dim3(n_tiles, tb.n_chains), W, rows_lds * W, stream>>>(tb.params, tb.L, tb.M, tb.pitch,
-                                                                                 tb.rows, tb.cost, tb.dec, w);
-        return;
-    }
-    const int n_inner = level + 1 >= kInnerLevel && n_tiles > 1 ? kG * (level + 1) - 3 * kG + 1 : 0;
+    // the edges begin with a launch of inner splits alone
+    const int n_tiles = step >= 0 ? steps.count(step) : 0, n_next = steps.count(step + 1);
     const TileWindows tw = tile_windows(tb, (int64_t)n_tiles * tb.n_chains);
     // how the next launch reads the inner results this one leaves
-    const TileWindows next = tile_windows(tb, (int64_t)(n_tiles - 1) * tb.n_chains);
-    int waves = tw.W / 64, n_kw = 1, inner_wgs = 0;
+    const TileWindows next = tile_windows(tb, (int64_t)n_next * tb.n_chains);
+    const int n_inner = n_next <= 0 ? 0 : edge ? 1 : max(0, kG * (step + 1) - 3 * kG + 1);
+    int waves = n_tiles > 0 ? tw.W / 64 : min(chunks, 4), n_kw = 1, inner_wgs = 0;
     if (n_inner > 0) {
-        // waves of the inner splits: about 1024, at least 4 splits each (measured: 512
-        // and 2048 lose 5% at L = 339, M = 500 and ten chains of L = 101)
-        const int64_t units = (int64_t)(n_tiles - 1) * chunks * tb.n_chains;
-        while (n_kw < kTileMaxWaves && units * n_kw < 1024 && n_inner >= 8 * n_kw)
+        // waves of the inner splits: about 1024, at least 4 splits each
+        // (measured: 512 and 2048 lose 5% at L = 339, M = 500 and ten chains of
+        // L = 101)
+        const int64_t units = (int64_t)n_next * chunks * tb.n_chains;
+        auto rounded = [&](int kw) { return (waves + kw - 1) / kw * kw; };
+        while (n_kw < 8 && units * n_kw < 1024 && n_inner >= 8 * n_kw && rounded(2 * n_kw) <= kTileMaxWaves)
             n_kw *= 2;
-        waves = (waves + n_kw - 1) / n_kw * n_kw;
+        waves = rounded(n_kw);
         const int bw = waves / n_kw;
-        inner_wgs = (chunks + bw - 1) / bw * (n_tiles - 1);
+        inner_wgs = (chunks + bw - 1) / bw * n_next;
     }
     const int threads = 64 * waves;
-    const size_t lds = max(rows_lds * tw.W,
+    const size_t lds = max(2 * kG * sizeof(int64_t) * (size_t)(n_tiles > 0 ? tw.W : 0),
                            n_kw > 1 ? kG * kG * sizeof(int64_t) * (size_t)(threads / n_kw) : 0);
-    (level >= kInnerLevel ? tile_kernel<true> : tile_kernel<false>)<<<dim3(n_tiles * tw.n_v + inner_wgs, tb.n_chains),
-                                                                      threads, lds, stream>>>(
-        tb.params, tb.L, tb.M, tb.pitch, tb.rows, level, tw.W, tw.halo, tw.n_v, next.n_v > 1 ? next.W : 0,
-        next.halo, n_kw, tb.cost, tb.dec, w);
+    const auto kernel = edge ? tile_kernel<true, true>
+                             : step >= kInnerLevel ? tile_kernel<true, false> : tile_kernel<false, false>;
+    kernel<<<dim3(n_tiles * tw.n_v + inner_wgs, tb.n_chains), threads, lds, stream>>>(
+        tb.params, tb.L, tb.M, tb.pitch, tb.rows, steps, step, n_tiles, tw.W, tw.halo, tw.n_v,
+        next.n_v > 1 ? next.W : 0, next.halo, n_kw, tb.cost, tb.dec, w);
+}
+
+void launch_tile_edges(int step, int delta, hipStream_t stream, const Tables &tb, const Work &w)
+{
+    launch_step(TileSteps{kBlockEdges, (tb.L + kG - 1) / kG, delta}, step, stream, tb, w);
+}
+
+void launch_tiles(int level, bool in_blocks, hipStream_t stream, const Tables &tb, const Work &w)
+{
+    const int groups = (tb.L + kG - 1) / kG;
+    if (level == 0) {
+        const int W = 64 * min((tb.M + 64) / 64, 8);
+        triangle_kernel<<<dim3(groups, tb.n_chains), W, 2 * kG * sizeof(int64_t) * W, stream>>>(
+            tb.params, tb.L, tb.M, tb.pitch, tb.rows, tb.cost, tb.dec, w);
+        return;
+    }
+    launch_step(TileSteps{in_blocks ? kDiagonalBlocks : kAllTiles, groups, 0}, level, stream, tb, w);
 }
 
 }  // namespace rotor

@@ -63,3 +63,22 @@ def test_inner_runs():
     p = chaingen.random_chains(1, 150, seed=7)
     p[:, :2] *= 230
     check(p, 90)
+
+
+# the blocked order's edges by tiles: one block-diagonal and more, chains that
+# end inside a block and a tile, windows in turn and overlapping ones, the kinds
+# of keys and of stored middle partials
+@pytest.mark.parametrize("shift", [0, 14, 26])
+@pytest.mark.parametrize("n,L,M", [(1, 17, 70), (1, 32, 130), (2, 37, 300), (1, 50, 321), (1, 53, 900), (9, 64, 400),
+                                   (1, 70, 1600), (1, 35, 3300)])
+def test_tile_block_edges(n, L, M, shift):
+    p = chaingen.random_chains(n, L, seed=600 + L)
+    p[:, :2] <<= shift
+    for schedule in ("blocked", "serial"):
+        check(p, M, schedule)
+
+
+def test_tile_block_edges_past_the_overlap():
+    p = chaingen.random_chains(1, 52, seed=700)
+    p[:, 2:] *= 30
+    check(p, 1300, "blocked")
