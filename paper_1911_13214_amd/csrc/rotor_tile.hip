@@ -733,6 +733,8 @@ __device__ __forceinline__ bool tile_finish(const ChainRows &r, const ChainWork 
     // the high splits, C_2's of the row at hand
     Raw xl[kG][kG], yh[kG][kG];
     RowCells<P> c2;
+    // loaded beside the rim where the keys leave registers for it
+    constexpr bool kEarly = sizeof(typename Key::K) == 4;
     auto load_operands = [&]() {
         const char *x = tr.base + row_of(L, s0, s0) * tr.rb;  // (s0 + u, s0 + u)
 #pragma unroll
@@ -762,7 +764,8 @@ __device__ __forceinline__ bool tile_finish(const ChainRows &r, const ChainWork 
         TileKeys<Key> keys;
         keys.clear();
         rim.template load<0>(a, r, tr);
-        load_operands();
+        if constexpr (kEarly)
+            load_operands();
         rim.template relax<0>(keys, a, pre, S, mc);
         __builtin_amdgcn_sched_barrier(0);
         rim.template load<1>(b, r, tr);
@@ -784,12 +787,15 @@ __device__ __forceinline__ bool tile_finish(const ChainRows &r, const ChainWork 
                 }
             }
         };
-        if constexpr (INNER && P::kBytes == 4)
+        if constexpr (INNER && kEarly)
             load_inner();
         rim.template relax<1>(keys, b, pre, S, mc);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (INNER && P::kBytes == 8)  // fewer registers
-            load_inner();
+        if constexpr (!kEarly) {
+            if constexpr (INNER)
+                load_inner();
+            load_operands();
+        }
 #pragma unroll
         for (int i = 0; i < kG; ++i) {
             const uint64_t pfx = lane_of64(v64, 3) - lane_of64(v64, i);
