@@ -358,14 +358,15 @@ def reconstruct(d_params, n_chains: int, L: int, M: int, d_dec, chain: int, budg
     else:
         stream.synchronize()
     count, status = count.cpu().numpy(), status.cpu().numpy()
-    ops = ops.cpu().numpy()
+    # the longest sequence's operations, a small part of cap as a rule
+    ops = ops[:, :min(int(count.max(initial=0)), cap)].cpu().numpy()
     out = []
     for b in range(n):
         if status[b] == ROTOR_INFEASIBLE:
             out.append(None)
             continue
         _check(int(status[b]), "rotor_reconstruct")
-        out.append([(int(k), int(s)) for k, s in ops[b, :count[b]]])
+        out.append(list(map(tuple, ops[b, :count[b]].tolist())))
     return out
 
 
