@@ -74,7 +74,10 @@
 // block-diagonals up to D - 2 (all but the first and the last 16) need
 // nothing of D - 1: they run on a second stream beside the edges of D - 1
 // (latency-bound waves beside VALU-bound ones), and the remaining 32 follow
-// those edges, merged by atomic minimum.  A small table is instead filled in the
+// those edges, merged by atomic minimum.  In tables of up to 3e10 candidates,
+// and in the last block-diagonals of larger ones, 4 x 4 tiles take the low and
+// high ranges (and the corners) in 8 launches, and the diagonal blocks in 4
+// (rotor_tile.hip).  A small table is instead filled in the
 // streamed order: 4 x 4 tiles of pairs, one launch per tile-diagonal
 // (rotor_tile.hip).
 #include <mutex>

@@ -1,7 +1,8 @@
-// Streamed order of the table fill: 4 x 4 tiles of pairs, tile-diagonal by
-// tile-diagonal (Theorem 1, Section 4.2 of Beaumont et al., arXiv
-// 1911.13214).  The recurrence, the value paths and the saturated budgets
-// are described at the head of rotor_fill.hip.
+// 4 x 4 tiles of pairs (Theorem 1, Section 4.2 of Beaumont et al., arXiv
+// 1911.13214): the streamed order of small tables, tile-diagonal by
+// tile-diagonal, and the diagonal blocks and edges of the blocked order.  The
+// recurrence, the value paths and the saturated budgets are described at the
+// head of rotor_fill.hip.
 //
 // Stages are cut into groups of 4; tile (R, C) holds the pairs (s, t) with s
 // in group R and t in group C.  triangle_kernel fills the diagonal tiles
@@ -10,7 +11,9 @@
 // launches.  The splits k of a tile's cells fall in
 //   middle  k in [4R + 4, 4C]: both operands in finished tiles, the same range
 //           for every cell: a 4 x 4 register product, 8 loads per 16
-//           candidates, on packed keys;
+//           candidates, on packed keys.  All but the first and last four (the
+//           rim) read no tile of the tile-diagonal before: these inner splits
+//           are taken one launch ahead by workgroups of their own;
 //   low     k in [s, 4R + 3]: X in the diagonal tile R, Y a cell of the same
 //           tile further down;
 //   high    k in [4C + 1, t - 1]: X a cell of the same tile to the left, Y in
@@ -18,16 +21,12 @@
 // Low and high splits (at most 6 per cell) and C_2 are taken row by row from
 // the tile's bottom row up, left to right in a row: a row's cells meet as X
 // in registers (same budget), and the rows above read them, shifted by the one w_a
-// their row is always shifted by, from LDS.  So a launch holds every budget of
-// a tile in one workgroup, 64 per wave, and meets at one barrier per row.
-//
-// Budgets past one workgroup's window: the cells of a row at budget m need
-// the rows below at no less than m - reach, reach being the largest sum of
-// shifts from a row down through the tile.  A window starts reach below its first
-// stored budget and computes those cells again (their operands outside the
-// tile are finished), so windows need nothing of each other; where reach
-// takes more than half a window, one workgroup walks all windows upwards
-// and reads the lower ones back instead.
+// their row is always shifted by, from LDS, with one barrier per row.
+// Measured on MI355X against one launch per t - s: L = 50, M = 500 202 -> 150 us,
+// L = 339, M = 500 5.7 -> 1.9 ms.  A launch is bound by the finishing wave's
+// dependent loads and about 2,500 instructions (8 to 12 us) and, in the middle
+// levels of long chains, by the inner splits' operands, 2 bytes per candidate
+// past the L2 at 4.4 TB/s.
 #include "rotor_paths.h"
 
 namespace rotor {
