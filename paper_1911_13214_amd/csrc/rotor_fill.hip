@@ -123,9 +123,13 @@ bool tiles_take(int L, int M) { return M < kTileBudgets || M <= kTileBudgetsPerS
 // 12.8 -> 10.6, L = 300, M = 5000 (2e10) 5.8 -> 5.2, 256 chains of L = 64, M = 640
 // 5.0 -> 4.2; L = 500, M = 2000 (4e10) 11.6 -> 11.4 with the last block-diagonals (up
 // to 200 waves of 64 budgets and blocks), 12.2 with all; L = 500, M = 5000 (1e11)
-// 17.96 -> 17.89 and 22.2.
+// 17.96 -> 17.89 and 22.2.  Chains of few blocks have few middle splits per edge
+// cell, so larger batches of them go by tiles too: 256 chains of L = 130, M = 1000
+// (9e10) 39.5 -> 33.2 ms, 200 of L = 100 17.6 -> 14.3, 50 of L = 200 20.3 -> 19.2;
+// 12 of L = 300 14.2 -> 14.5, 5 of L = 320, M = 2000 12.5 -> 13.5 (not by tiles).
 constexpr uint64_t kTileEdgeCandidates = 30000000000ull;
 constexpr int kTileEdgeWaves = 200;
+constexpr int kTileEdgeBlocks = 13;
 constexpr int kSplitMinD = 16;  // diagonals from this length spread their splits over four waves
 
 // ---------------------------------------------------------------------------
@@ -2086,14 +2090,14 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
         return tile_diagonals(false);
     const int nb = (L + kT - 1) / kT;
     // Edges of block-diagonal delta by tiles, 8 launches instead of 30: all in
-    // tables of up to 3e10 candidates, whose edges outweigh the middle products;
+    // tables of up to 3e10 candidates or 13 blocks, whose edges outweigh the middle products;
     // in larger ones, where the products run beside them, the last
     // block-diagonals, whose rounds are bound by their launches.  From the first
     // such block-diagonal on all are (they have ever fewer blocks), so the
     // 2-byte copy, which the tiles' windows overwrite, is no longer read.
     auto tile_edges = [&](int delta) {
         return schedule != ROTOR_SCHEDULE_BLOCKED_ROWS && schedule != ROTOR_SCHEDULE_BLOCKED_ROUNDS &&
-               (r_total <= kTileEdgeCandidates || (int64_t)(nb - delta) * mb64 * tb.n_chains <= kTileEdgeWaves);
+               (r_total <= kTileEdgeCandidates || nb <= kTileEdgeBlocks || (int64_t)(nb - delta) * mb64 * tb.n_chains <= kTileEdgeWaves);
     };
     if (!streamed && tile_edges(1)) {
         if ((e = tile_diagonals(true)) != hipSuccess)

@@ -82,3 +82,18 @@ def test_tile_block_edges_past_the_overlap():
     p = chaingen.random_chains(1, 52, seed=700)
     p[:, 2:] *= 30
     check(p, 1300, "blocked")
+
+
+def test_tile_block_edges_of_large_batches():
+    # past 3e10 candidates short chains keep edges by tiles: the same tables as
+    # by rows, which other tests hold against the oracle
+    import torch
+
+    from gpu_util import solve_on_gpu
+    n, L, M = 256, 100, 760
+    p = chaingen.random_chains(n, L, seed=900)
+    print(f"tiles L={L} M={M} n={n}", flush=True)
+    _, cost, dec = solve_on_gpu(p, M)
+    _, cost_rows, dec_rows = solve_on_gpu(p, M, schedule="rows")
+    assert torch.equal(cost[..., :M + 1], cost_rows[..., :M + 1])
+    assert torch.equal(dec[..., :M + 1], dec_rows[..., :M + 1])
