@@ -229,7 +229,7 @@ ROTOR_API int32_t rotor_solve_status(const void *d_work, uint64_t work_bytes, in
  *                            blocks; the splits inside the block's own rows
  *                            and columns ("edges") by 4 x 4 tiles (8 launches
  *                            per block-diagonal) in tables of up to 3e10
- *                            candidates and for the last block-diagonals of
+ *                            candidates, chains of up to 13 blocks and for the last block-diagonals of
  *                            larger ones, else by rows (16 launches) when a
  *                            block-diagonal holds at least 256 blocks over
  *                            all chains, else by anti-diagonals (30 short
