@@ -228,19 +228,24 @@ ROTOR_API int32_t rotor_solve_status(const void *d_work, uint64_t work_bytes, in
  *                            products for the splits that reach across
  *                            blocks; the splits inside the block's own rows
  *                            and columns ("edges") by 4 x 4 tiles (8 launches
- *                            per block-diagonal) in tables of up to 3e10
- *                            candidates, chains of up to 13 blocks and for the last block-diagonals of
- *                            larger ones, else by rows (16 launches) when a
- *                            block-diagonal holds at least 256 blocks over
- *                            all chains, else by anti-diagonals (30 short
- *                            launches); the fast order for large tables.
+ *                            per block-diagonal, up to 2 more where sizes are
+ *                            large against the budgets) in tables of up to
+ *                            3e10 candidates, chains of up to 13 blocks and
+ *                            for the last block-diagonals of larger ones, if
+ *                            M < 1024, M <= 8 L, or M < 2048 and M <= 24 L;
+ *                            else by rows (16 launches) when a block-diagonal
+ *                            holds at least 256 blocks over all chains, else
+ *                            by anti-diagonals (30 short launches); the fast
+ *                            order for large tables.
  *   ROTOR_SCHEDULE_DIAGONAL  4 x 4 tiles of pairs, one launch per
- *                            tile-diagonal (ceil(L / 4) of them), the splits
- *                            that a tile shares as register products; from
- *                            M = 512 on, when M > 24 L, one launch per t - s
- *                            over all pairs, the splits of a pair spread over
- *                            four waves from t - s = 16 on; few launches, the
- *                            fast order for small tables.
+ *                            tile-diagonal (ceil(L / 4) of them, and one per
+ *                            640 budgets or fewer), the splits that a tile
+ *                            shares as register products; from M = 320 on,
+ *                            for the shortest chains and where M > 24 L (from
+ *                            M = 1024 on; from 512 on below 20 stages), one
+ *                            launch per t - s over all pairs, the splits of a
+ *                            pair spread over four waves from t - s = 16 on;
+ *                            few launches, the fast order for small tables.
  *   ROTOR_SCHEDULE_AUTO      DIAGONAL when the table has at most 1.8e10 split
  *                            candidates (L^3/6 (M+1)) for one chain with
  *                            M < 1024, 8e9 for one with more budgets, 7e9

@@ -110,26 +110,46 @@ constexpr uint64_t kStreamMaxCandidatesN = 400000000ull;
 constexpr int kStreamBelowBudgets = 64;
 
 // The streamed order goes by tiles unless the budgets are so many, against the
-// stages, that sizes taken from them (a chain's sizes add up to about the
-// budgets, more where its memory is short) would reach past the tiles'
-// overlapping windows, which are then filled in turn: it then goes diagonal by
-// diagonal, one launch each (measured on MI355X, tiles against diagonals:
-// L = 100, M = 5000 2.3 / 1.4 ms, L = 60, M = 3000 0.78 / 0.34 ms, L = 20, M = 1431
-// 144 / 92 us; L = 200, M = 3000 1.8 / 3.3 ms, L = 100, M = 1000 0.32 / 0.51 ms).
-constexpr int kTileBudgets = 512, kTileBudgetsPerStage = 24;
-bool tiles_take(int L, int M) { return M < kTileBudgets || M <= kTileBudgetsPerStage * L; }
+// stages, that the launches of a chain whose windows lie apart (ceil(L / 4) and
+// one per window past the first, about 8/3 as long as a diagonal's) lose to the
+// L of the diagonals.  Measured on MI355X, tiles against diagonals, for sizes
+// from a memory limit of half of store-everything (windows apart) and for sizes
+// of 1 to 40 (overlapping): L = 8, M = 500 33 / 34 us, 26 / 34; L = 9, M = 500 42 / 38,
+// 34 / 37; L = 12, M = 500 46 / 51, 37 / 50; L = 13, M = 500 58 / 56, 48 / 55; L = 20,
+// M = 500 70 / 86, 57 / 84; L = 20, M = 1000 79 / 87, 60 / 82; L = 20, M = 1500 96 / 87;
+// L = 24, M = 700 99 / 103; L = 32, M = 1500 136 / 135; L = 64, M = 1500 246 / 308,
+// 210 / 282; L = 100, M = 2400 0.44 / 0.86 ms, 0.35 / 0.62; L = 200, M = 4500 3.0 / 3.4.
+constexpr int kTileBudgetsPerStage = 24;
+bool tiles_take(int L, int M)
+{
+    if (M < 320)  // one window
+        return true;
+    const int groups = (L + kTileSide - 1) / kTileSide, launches = groups + (groups > 1 ? 1 : 0);
+    if (launches > 1 && 8 * launches > 3 * L)
+        return false;
+    return M < (L >= 20 ? 1024 : 512) || M <= kTileBudgetsPerStage * L;
+}
 // Blocked edges by tiles (launch_fill), measured on MI355X against the rounds (rows
-// for the batch): L = 500, M = 1000 (2e10) 9.2 -> 7.5 ms, L = 700, M = 500 (3e10)
-// 12.8 -> 10.6, L = 300, M = 5000 (2e10) 5.8 -> 5.2, 256 chains of L = 64, M = 640
-// 5.0 -> 4.2; L = 500, M = 2000 (4e10) 11.6 -> 11.4 with the last block-diagonals (up
-// to 200 waves of 64 budgets and blocks), 12.2 with all; L = 500, M = 5000 (1e11)
-// 17.96 -> 17.89 and 22.2.  Chains of few blocks have few middle splits per edge
-// cell, so larger batches of them go by tiles too: 256 chains of L = 130, M = 1000
-// (9e10) 39.5 -> 33.2 ms, 200 of L = 100 17.6 -> 14.3, 50 of L = 200 20.3 -> 19.2;
-// 12 of L = 300 14.2 -> 14.5, 5 of L = 320, M = 2000 12.5 -> 13.5 (not by tiles).
+// for batches): L = 500, M = 1000 (2e10) 9.0 -> 7.5 ms, L = 700, M = 500 (3e10)
+// 12.7 -> 10.2, L = 300, M = 2000 with 8-byte values 6.9 -> 5.6, 256 chains of L = 64,
+// M = 640 5.0 -> 3.9.  In larger tables the last block-diagonals, up to 200 waves of
+// 64 budgets and blocks: L = 1001, M = 200 (3.4e10) 17.8 -> 13.2 ms, L = 700, M = 700
+// 13.8 -> 12.6, L = 450, M = 2400 10.0 -> 9.7; with all of them L = 500, M = 2000
+// (4e10) 11.6 -> 12.2.  Chains of few blocks have few middle splits per edge cell, so
+// larger batches of them go by tiles too: 256 chains of L = 130, M = 1000 (9e10)
+// 39.5 -> 30.5 ms, 200 of L = 100 18.1 -> 13.1, 50 of L = 200 21.2 -> 18.1; 12 of L = 300
+// 14.2 -> 14.5, 5 of L = 320, M = 2000 12.5 -> 13.5 (not by tiles).
 constexpr uint64_t kTileEdgeCandidates = 30000000000ull;
-constexpr int kTileEdgeWaves = 200;
 constexpr int kTileEdgeBlocks = 13;
+constexpr int kTileEdgeWaves = 200;
+// Budgets up to which they are: windows that lie apart add launches to the 8 of a
+// block-diagonal, and the waves of many budgets fill the chip whichever way.  Sizes
+// from a limit of half and of a tenth of store-everything, rounds -> tiles: L = 250,
+// M = 1500 3.9 -> 2.9 and 4.0 -> 3.8 ms, M = 2000 4.0 -> 3.1, 4.1 -> 4.1; L = 300, M = 2400
+// 5.3 -> 4.5, 5.7 -> 5.8; L = 150, M = 5000 2.5 -> 3.3, 2.7 -> 3.6; L = 100, M = 20000
+// 2.4 -> 6.3 ms; 16 chains of L = 64, M = 2047 1.4 -> 1.8, 1.6 -> 2.0; 256 of L = 35,
+// M = 1000 3.4 -> 2.7, 3.3 -> 2.7.
+constexpr int kTileEdgeBudgets = 1024, kTileEdgeBudgetsPerStage = 8;
 constexpr int kSplitMinD = 16;  // diagonals from this length spread their splits over four waves
 
 // ---------------------------------------------------------------------------
@@ -198,7 +218,8 @@ __global__ __launch_bounds__(64) void prep_kernel(const int64_t *__restrict__ pa
         // PP and B the sums of P and of u_b up to a stage,
         // V(x + 1, y) = sum_{l=x+1}^{y} (P[l] - P[x]) + B[y] - B[x]
         //             = PP[y] - PP[x] - (y - x) P[x] + B[y] - B[x];
-        // bsum keeps PP and B at the block ends min(16b, L), b = 0..nb.
+        // bsum keeps PP and B at the block ends min(16b, L), b = 1..nb (both
+        // are 0 at b = 0, and PP's word there holds the chain's reach).
         const int nb = (L + kT - 1) / kT;
         int32_t *pb = w.pbits + (int64_t)c * nb;
         int64_t *ppb = w.bsum + (int64_t)c * 2 * (nb + 1);
@@ -236,16 +257,14 @@ __global__ __launch_bounds__(64) void prep_kernel(const int64_t *__restrict__ pa
             carry_p = __shfl(vp, 63);
             carry_b = __shfl(vb, 63);
         }
-        if (lane == 0) {
-            ppb[0] = 0;
+        if (lane == 0)
             bb[0] = 0;
-        }
         __syncthreads();
         for (int D = lane; D < nb; D += 64) {
             int64_t vmax = 0;  // below 2^45 in the domain
             for (int I = 0; I + D < nb; ++I) {
                 const int x = I * kT, yb = I + D + 1, y = min(yb * kT, L);
-                vmax = max(vmax, ppb[yb] - ppb[I] - (int64_t)(y - x) * pre[x] + bb[yb] - bb[I]);
+                vmax = max(vmax, ppb[yb] - (I > 0 ? ppb[I] : 0) - (int64_t)(y - x) * pre[x] + bb[yb] - bb[I]);
             }
             // (V_D + 1) << S <= 2^32 - 1 leaves S >= 0 bits on the narrow path;
             // -2 marks a 64-bit block-diagonal whose middle keys are exact as
@@ -263,11 +282,32 @@ __global__ __launch_bounds__(64) void prep_kernel(const int64_t *__restrict__ pa
         return;
     }
     const int s = blockIdx.x + 1;
+    auto clamp_shift = [&](int64_t v) { return (int32_t)(v < 0 ? 0 : v > (int64_t)M + 1 ? (int64_t)M + 1 : v); };
     if (lane == 0) {
-        auto clamp_shift = [&](int64_t v) { return (int32_t)(v < 0 ? 0 : v > (int64_t)M + 1 ? (int64_t)M + 1 : v); };
         int32_t *sh = w.shift + (int64_t)c * 2 * L;
         sh[s - 1] = clamp_shift(r.wa[s - 1]);
         sh[L + s - 1] = clamp_shift(r.wabar[s - 1]);
+    }
+    if (s == L) {
+        // The chain's reach (ChainWork::reach): down the four rows of a tile,
+        // split candidates shift by w_a of the stage before the lower row, C_2
+        // by the row's own w_abar.
+        int most = 0;
+        for (int s0 = lane * kTileSide; s0 + kTileSide < L; s0 += 64 * kTileSide) {
+            int reach[kTileSide] = {};
+#pragma unroll
+            for (int i = kTileSide - 2; i >= 0; --i) {
+                reach[i] = clamp_shift(r.wabar[s0 + i]) + reach[i + 1];
+#pragma unroll
+                for (int e = i + 1; e < kTileSide; ++e)
+                    reach[i] = max(reach[i], clamp_shift(r.wa[s0 + e - 1]) + reach[e]);
+                most = max(most, reach[i]);
+            }
+        }
+        for (int off = 1; off < 64; off *= 2)
+            most = max(most, __shfl_xor(most, off));
+        if (lane == 0)
+            w.bsum[(int64_t)c * 2 * ((L + kT - 1) / kT + 1)] = most;
     }
     int32_t *gn = w.gnone + (int64_t)c * rows;
     int32_t *ga = w.gall + (int64_t)c * rows;
@@ -2062,17 +2102,18 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
         (schedule == ROTOR_SCHEDULE_AUTO && (r_total <= stream_max || (nc == 1 && W < (uint64_t)kStreamBelowBudgets)));
     // Tile-diagonals (rotor_tile.hip), the first with the leaves: all of them
     // (streamed), or those inside the diagonal blocks.
-    auto tile_diagonals = [&](bool in_blocks) -> hipError_t {
+    auto tile_diagonals = [&](TileSet set) -> hipError_t {
         const int groups = (L + kTileSide - 1) / kTileSide;
-        for (int level = 0; level < (in_blocks ? min(groups, kT / kTileSide) : groups); ++level) {
+        for (TileRun run(tb, set); run.more();) {
+            const int level = run.step();
             const KernelClass k = level == 0 ? kLeaf : kDiag;
             hipError_t e = before(k);
             if (e != hipSuccess)
                 return e;
-            launch_tiles(level, in_blocks, stream, tb, w);
+            run.launch(stream, w);
             uint64_t c1 = 0, c2 = 0, cells = 0;
-            for (int R = 0; obs && R + level < groups; ++R) {
-                if (in_blocks && R % (kT / kTileSide) + level >= kT / kTileSide)
+            for (int R = 0; obs && level >= 0 && R + level < groups; ++R) {
+                if (set == kDiagonalBlocks && R % (kT / kTileSide) + level >= kT / kTileSide)
                     continue;
                 for (int s = R * kTileSide + 1; s <= min((R + 1) * kTileSide, L); ++s)
                     for (int t = max(s, (R + level) * kTileSide + 1); t <= min((R + level + 1) * kTileSide, L); ++t) {
@@ -2087,20 +2128,20 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
         return hipSuccess;
     };
     if (streamed && tiles)
-        return tile_diagonals(false);
+        return tile_diagonals(kAllTiles);
     const int nb = (L + kT - 1) / kT;
-    // Edges of block-diagonal delta by tiles, 8 launches instead of 30: all in
-    // tables of up to 3e10 candidates or 13 blocks, whose edges outweigh the middle products;
-    // in larger ones, where the products run beside them, the last
-    // block-diagonals, whose rounds are bound by their launches.  From the first
-    // such block-diagonal on all are (they have ever fewer blocks), so the
+    // Edges of block-diagonal delta by tiles, 8 launches instead of 30.  From the
+    // first such block-diagonal on all are (they have ever fewer blocks), so the
     // 2-byte copy, which the tiles' windows overwrite, is no longer read.
+    const bool edge_budgets = tb.M < kTileEdgeBudgets || tb.M <= kTileEdgeBudgetsPerStage * L ||
+                              (tb.M < 2 * kTileEdgeBudgets && tb.M <= kTileBudgetsPerStage * L);
     auto tile_edges = [&](int delta) {
-        return schedule != ROTOR_SCHEDULE_BLOCKED_ROWS && schedule != ROTOR_SCHEDULE_BLOCKED_ROUNDS &&
-               (r_total <= kTileEdgeCandidates || nb <= kTileEdgeBlocks || (int64_t)(nb - delta) * mb64 * tb.n_chains <= kTileEdgeWaves);
+        return schedule != ROTOR_SCHEDULE_BLOCKED_ROWS && schedule != ROTOR_SCHEDULE_BLOCKED_ROUNDS && edge_budgets &&
+               (r_total <= kTileEdgeCandidates || nb <= kTileEdgeBlocks ||
+                (int64_t)(nb - delta) * mb64 * tb.n_chains <= kTileEdgeWaves);
     };
     if (!streamed && tile_edges(1)) {
-        if ((e = tile_diagonals(true)) != hipSuccess)
+        if ((e = tile_diagonals(kDiagonalBlocks)) != hipSuccess)
             return e;
     } else {
         if ((e = before(kLeaf)) != hipSuccess)
@@ -2245,10 +2286,10 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
                 return e;
             inner_done = next_inner;
             if (tile_edges(delta)) {
-                constexpr int kSide = kT / kTileSide;
-                for (int q = -1; q <= 2 * kSide - 2; ++q) {
+                for (TileRun run(tb, kBlockEdges, delta); run.more();) {
+                    const int q = run.step();
                     uint64_t c1 = 0, cells = 0;
-                    for (int I = 0; obs && I + delta < nb; ++I)
+                    for (int I = 0; obs && q >= 0 && I + delta < nb; ++I)
                         for (int a = 0; a < kT; ++a)
                             for (int b = 0; b < min(kT, L - (I + delta) * kT); ++b)
                                 if (a / kTileSide + b / kTileSide == q) {
@@ -2257,7 +2298,7 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
                                 }
                     if ((e = before(kEdge)) != hipSuccess)
                         return e;
-                    launch_tile_edges(q, delta, stream, tb, w);
+                    run.launch(stream, w);
                     if ((e = launched(kEdge, c1, cells, cells)) != hipSuccess)
                         return e;
                 }

@@ -34,7 +34,8 @@ struct Work {
     int64_t *pre;      // [n_chains][L + 1]
     int64_t *preall;   // [n_chains][L + 1]: prefix sums of u_f + u_b
     int32_t *pbits;    // [n_chains][nb], nb = ceil(L / 16): packed key bits of block-diagonal D, -1: 64-bit path
-    int64_t *bsum;     // [n_chains][2][nb + 1]: sums of prefix sums of u_f, and of u_b, to block ends
+    int64_t *bsum;     // [n_chains][2][nb + 1]: sums of prefix sums of u_f, and of u_b, to block ends; a
+                       // chain's first word (0 as a sum) is its reach (ChainWork::reach)
     int32_t *gnone;    // [n_chains][rows]
     int32_t *gall;     // [n_chains][rows]
     int32_t *gsat;     // [n_chains][rows]: G(s, t), clamped like the gates
@@ -107,14 +108,34 @@ struct LaunchObserver {
 hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_t stream,
                        LaunchObserver *obs = nullptr, bool side_stream = true);
 
-// Tiles of kTileSide x kTileSide pairs (rotor_tile.hip): the launch of one
-// tile-diagonal (level = 0: the diagonal tiles with the leaves), of all tiles
-// (the streamed fill) or of those inside the diagonal blocks; and one step of
-// the edges of the blocks of one block-diagonal, the tiles a + b = step of each:
-// steps -1 (which prepares step 0) to 2 kBlock / kTileSide - 2.
+// Tiles of kTileSide x kTileSide pairs (rotor_tile.hip), in steps that depend
+// on the ones before: all tiles by tile-diagonals (the streamed fill), those
+// inside the diagonal blocks by tile-diagonals (step 0 of both: the diagonal
+// tiles with the leaves), or the edges of the blocks of block-diagonal delta,
+// the tiles a + b = step of each.
 constexpr int kTileSide = 4;
-void launch_tiles(int level, bool in_blocks, hipStream_t stream, const Tables &tb, const Work &w);
-void launch_tile_edges(int step, int delta, hipStream_t stream, const Tables &tb, const Work &w);
+enum TileSet { kAllTiles, kDiagonalBlocks, kBlockEdges };
+
+// The launches that fill a set of tiles:
+//   for (TileRun r(tb, set, delta); r.more();) r.launch(stream, w);
+// A step's budgets may be cut into windows; those of chains whose sizes reach
+// too far for one launch to fill them all (Work::bsum) take one launch each,
+// beside the windows below of the steps that follow.
+class TileRun {
+public:
+    TileRun(const Tables &tb, TileSet set, int delta = 0);
+    bool more() const;
+    // the step whose first window the next launch takes (-1: none)
+    int step() const;
+    void launch(hipStream_t stream, const Work &w);
+
+private:
+    const Tables &tb;
+    TileSet set_;
+    int delta_, groups_;
+    int front_, first_, last_;  // next launch's first window; the steps of the present windows
+    int n_apart_ = 1;  // its windows of chains whose windows lie side by side
+};
 
 // Edges of the blocked fill by rows: whether a block-diagonal with `blocks`
 // blocks over all chains takes them, and the launch of row 16(I + 1) - a of

@@ -116,6 +116,10 @@ struct ChainWork {
                            // or, if V_D >= 2^32 - 1 (64-bit path), -2 while V_D < 2^38, else -1
     int16_t *half;         // [16 L][hpitch] 2-byte copy of the diagonal blocks' cells
     int64_t hpitch;
+    const int64_t *reach_at;
+    // The largest sum of shifts from a row of a 4 x 4 tile down through it: how
+    // far below its own budget a cell reads other cells of its tile.
+    __device__ int reach() const { return (int)*(const_i64)reach_at; }
     // whether the pairs of block-diagonal D take the narrow path
     __device__ bool narrow(int D) const { return pbits[D] >= 0; }
     // whether the middle keys value * 2^15 + (split offset) of block-diagonal
@@ -149,6 +153,7 @@ __device__ inline ChainWork chain_work(const Work &w, int L, int64_t rows, int64
     cw.shadow = w.shadow + (int64_t)c * rows * pitch;
     cw.pbits = w.pbits + (int64_t)c * ((L + kT - 1) / kT);
     cw.hpitch = half_pitch_of(pitch);
+    cw.reach_at = w.bsum + (int64_t)c * 2 * (cw.nb + 1);
     cw.half = w.half + (int64_t)c * L * kT * cw.hpitch;
     return cw;
 }

@@ -8,7 +8,8 @@
 // in group R and t in group C.  triangle_kernel fills the diagonal tiles
 // (R, R), leaves included; then one launch of tile_kernel per C - R = 1, 2,
 // ... fills the others, so a chain of L stages takes ceil(L / 4) dependent
-// launches.  The splits k of a tile's cells fall in
+// launches, and one more per further window of budgets where the chain's sizes
+// are large against them (Window).  The splits k of a tile's cells fall in
 //   middle  k in [4R + 4, 4C]: both operands in finished tiles, the same range
 //           for every cell: a 4 x 4 register product, 8 loads per 16
 //           candidates, on packed keys.  All but the first and last four (the
@@ -27,6 +28,8 @@
 // dependent loads and about 2,500 instructions (8 to 12 us) and, in the middle
 // levels of long chains, by the inner splits' operands, 2 bytes per candidate
 // past the L2 at 4.4 TB/s.
+#include <climits>
+
 #include "rotor_paths.h"
 
 namespace rotor {
@@ -103,13 +106,14 @@ struct Key64 {
 };
 
 // Budgets of one pass over a tile: W from w0 on, 64 per wave, stored from
-// `from` on.  A tile of more budgets is filled by workgroups of overlapping
-// windows, W - halo apart: a row's cells at budget m need the rows below at no
-// less than m - reach (tile_reach), so a window whose rows reach no further
-// than halo finds what it stores in itself, computing its first halo budgets a
-// second time, and waits for no other.  Where the rows reach
-// further, the first workgroup walks all windows upwards (w0 a multiple of W)
-// and reads the lower ones back from the tables.
+// `from` on.  A row's cells at budget m need the rows below at no more than m
+// and no less than m - reach (the chain's reach: the largest sum of shifts
+// down through the rows of a tile).  Where the reach is no more than `halo`, a
+// tile's windows overlap by that much: a window computes its first halo budgets
+// a second time, finds what it stores in itself and waits for no other, so all
+// windows of a tile are filled in one launch.  Elsewhere the windows lie side by
+// side, each one launch after the one below, and read what lies below them
+// back from the tables.
 struct Window {
     int W, halo, w0, from;
     bool back;  // what lies below w0 is read back
@@ -462,25 +466,6 @@ __device__ __forceinline__ uint64_t lane_of64(int64_t v, int l)
            (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), l) << 32;
 }
 
-// The largest sum of shifts from a row of the tile down through it: low
-// splits shift by w_a of the stage before the lower row, C_2 by the row's own
-// w_abar.  v32 as in tile_finish.
-__device__ __forceinline__ int tile_reach(int32_t v32)
-{
-    int reach[kG];
-    reach[kG - 1] = 0;
-    int most = 0;
-#pragma unroll
-    for (int i = kG - 2; i >= 0; --i) {
-        reach[i] = lane_of(v32, 36 + i) + reach[i + 1];
-#pragma unroll
-        for (int e = i + 1; e < kG; ++e)
-            reach[i] = max(reach[i], lane_of(v32, 32 + e) + reach[e]);
-        most = max(most, reach[i]);
-    }
-    return most;
-}
-
 // Whether every cell of the tile is saturated at every budget from `base` on
 // (G(s, t) falls as s grows, so the tile's first row has the largest).
 __device__ inline bool tile_saturated(const ChainRows &r, const ChainWork &cw, int L, int s0, int t0, int base)
@@ -500,21 +485,26 @@ __device__ inline bool tile_saturated(const ChainRows &r, const ChainWork &cw, i
 // Inner results at the budgets that a second window computes again (the first
 // halo of every window but the first) are kept twice: in the cost slots, which
 // the window that stores those cells overwrites, and for the three lower rows
-// in the workspace's 2-byte section, which this order has no other use for: 128
-// half_pitch bytes per tile, half of them for each parity of its
-// tile-diagonal.  Budgets come in waves of 64.
+// in the workspace's 2-byte section, which the tiles have no other use for: 128
+// half_pitch bytes per tile row group (16 rows of the section per stage, so a
+// chain's tiles fit), half of them for each parity of its tile-diagonal.
+// Budgets come in waves of 64.
 __device__ inline int halo_place(int base, int W, int halo)
 {
     const int per = (W - halo) >> 6, own = halo >> 6;
     const int q = base >> 6, v = q / per, x = q - v * per;
     return v > 0 && x < own ? ((v - 1) * own + x) * 64 : -1;
 }
+constexpr int kHaloRows = (kG - 1) * kG;
+constexpr int kHaloSlice = kG * kT;  // rows of the 2-byte section per row group
+// places of a row's halos: room for halos of up to 2/3 of W - halo
+__device__ inline int64_t halo_pitch_of(const ChainWork &cw) { return cw.hpitch * 2 / 3 / 64 * 64; }
+static_assert(2 * kHaloRows * 2 * sizeof(int64_t) <= 3 * kHaloSlice * sizeof(int16_t), "halos of both parities in a slice");
 __device__ inline int64_t *halo_of(const ChainWork &cw, int R, int level)
 {
-    // 12 rows of halo_pitch_of words: room for halos of up to 2/3 of W - halo
-    return (int64_t *)(cw.half + (int64_t)R * (64 * cw.hpitch)) + (level & 1) * (8 * cw.hpitch);
+    return (int64_t *)(cw.half + (int64_t)R * (kHaloSlice * cw.hpitch)) +
+           (level & 1) * (kHaloSlice * sizeof(int16_t) / sizeof(int64_t) / 2 * cw.hpitch);
 }
-__device__ inline int64_t halo_pitch_of(const ChainWork &cw) { return cw.hpitch * 2 / 3 / 64 * 64; }
 
 // tile_inner's part for the edges of the blocked order: the splits of a tile of
 // block (I, J) inside the block, less the rim, k in [4R + 8, 16I + 15] and [16J + 1,
@@ -652,13 +642,12 @@ __device__ __forceinline__ void tile_inner(const ChainRows &r, const ChainWork &
 // One window of tile (R, C), C > R: the splits of its cells that tile_inner
 // did not take, C_2, the gates, the final cells.  Bound by latency and, from
 // about five waves in a workgroup on, by instruction issue: the scalars of the
-// tile come in two vector loads, then the operands in two batches.  INNER:
-// tile_inner has left its results.  Returns whether the rows reach further
-// than a halo.
+// tile come in two vector loads, then the operands in two batches.  has_inner:
+// tile_inner has left its results.
 template <class Key, bool INNER>
-__device__ __forceinline__ bool tile_finish(const ChainRows &r, const ChainWork &cw, int L, int M, int64_t pitch,
-                                            int R, int C, int S, const Window &wn, int64_t *tab, int16_t *dtab,
-                                            char *lds)
+__device__ __forceinline__ void tile_finish(const ChainRows &r, const ChainWork &cw, int L, int M, int64_t pitch,
+                                            int R, int C, int S, bool has_inner, const Window &wn, int64_t *tab,
+                                            int16_t *dtab, char *lds)
 {
     typedef typename Key::P P;
     typedef typename P::Raw Raw;
@@ -704,10 +693,7 @@ __device__ __forceinline__ bool tile_finish(const ChainRows &r, const ChainWork 
     const const_i64 pre = (const_i64)cw.pre;
     // waves past M, and waves whose cells are all saturated, relax nothing
     const bool sat = base > M || tile_saturated(r, cw, L, s0, t0, base);
-    // a window of its own whose rows reach below it stores nothing: the tile's
-    // first workgroup fills those budgets
-    const bool far = tile_reach(v32) > wn.halo;
-    const bool in = m <= M && m >= wn.from && (wn.w0 == 0 || wn.back || !far);
+    const bool in = m <= M && m >= wn.from;
     if (sat) {
 #pragma unroll 1
         for (int i = kG - 1;; --i) {
@@ -722,7 +708,7 @@ __device__ __forceinline__ bool tile_finish(const ChainRows &r, const ChainWork 
                 st.next();
             }
             if (i == 0)
-                return far;
+                return;
             bufs[(i & 1) * wn.W + wn.at] = c;
             lds_barrier();
         }
@@ -770,20 +756,28 @@ __device__ __forceinline__ bool tile_finish(const ChainRows &r, const ChainWork 
         rim.template load<1>(b, r, tr);
         [[maybe_unused]] int64_t inner[kG][kG];
         auto load_inner = [&]() {
-            const int at = base < wn.from ? halo_place(base, wn.W, wn.halo) : -1;
-            const int64_t hp = halo_pitch_of(cw);
+            if (has_inner) {
+                const int at = base < wn.from ? halo_place(base, wn.W, wn.halo) : -1;
+                const int64_t hp = halo_pitch_of(cw);
 #pragma unroll
-            for (int i = 0; i < kG; ++i) {
-                // the first row of a halo is not needed
-                const bool copy = i > 0 && at >= 0;
-                const int64_t *q = copy ? halo_of(cw, R, C - R) + (i - 1) * kG * hp + at
-                                        : tab + row_of(L, s0 + i, t0) * pitch + base;
-                const int64_t step = copy ? hp : pitch;
+                for (int i = 0; i < kG; ++i) {
+                    // the first row of a halo is not needed
+                    const bool copy = i > 0 && at >= 0;
+                    const int64_t *q = copy ? halo_of(cw, R, C - R) + (i - 1) * kG * hp + at
+                                            : tab + row_of(L, s0 + i, t0) * pitch + base;
+                    const int64_t step = copy ? hp : pitch;
 #pragma unroll
-                for (int j = 0; j < kG; ++j) {
-                    inner[i][j] = load64(q, mc - base);
-                    q += j < last ? step : 0;
+                    for (int j = 0; j < kG; ++j) {
+                        inner[i][j] = load64(q, mc - base);
+                        q += j < last ? step : 0;
+                    }
                 }
+            } else {
+#pragma unroll
+                for (int i = 0; i < kG; ++i)
+#pragma unroll
+                    for (int j = 0; j < kG; ++j)
+                        inner[i][j] = -1;  // all ones: above every stored form
             }
         };
         if constexpr (INNER && kEarly)
@@ -855,7 +849,6 @@ __device__ __forceinline__ bool tile_finish(const ChainRows &r, const ChainWork 
                 relax_earlier<P>(acc[u][j], x, P::yop(v.v[j]), (uint32_t)s);
         }
     }
-    return far;
 }
 
 // The diagonal tile R: stages s0 .. s0 + last, leaves included (Eq.
@@ -916,31 +909,20 @@ __device__ __forceinline__ void triangle_body(const ChainRows &r, const ChainWor
     }
 }
 
-// The passes of workgroup `v` of a tile, n_v of them sharing its windows, as
-// Window describes; body(window, R) fills one and returns whether the rows
-// reach too far for windows of their own.  R is opaque in each pass, or the
-// compiler computes every row address of the tile before the loop and spills
-// them.
+// The passes of a workgroup over a tile's budgets from wn.w0 on, in turn;
+// body(wn, R) fills one.  R is opaque in each pass, or the compiler computes
+// every row address of the tile before the loop and spills them.
 template <class F>
-__device__ __forceinline__ void for_windows(int M, int W, int halo, int v, int n_v, int at, int R, F &&body)
+__device__ __forceinline__ void for_passes(Window &wn, int M, int passes, int R, F &&body)
 {
-    Window wn;
-    wn.W = W;
-    wn.at = at;
-    wn.back = false;
-    wn.halo = halo;
-    wn.w0 = v * (W - halo);
-    wn.from = v > 0 ? wn.w0 + halo : 0;
     for (;;) {
         wn.m = wn.w0 + wn.at;
         wn.mc = min(wn.m, M);
         int tile = R;
         asm volatile("" : "+s"(tile));
-        const bool far = body(wn, tile) || n_v == 1;
-        if (v > 0 || !far)
-            return;
-        wn.w0 += W;
-        if (wn.w0 > M)
+        body(wn, tile);
+        wn.w0 += wn.W;
+        if (--passes == 0 || wn.w0 > M)
             return;
         wn.from = wn.w0;
         wn.back = true;
@@ -960,12 +942,12 @@ __global__ __launch_bounds__(kTileMaxWaves * 64) void triangle_kernel(const int6
     const ChainWork cw = chain_work(w, L, rows, pitch, c);
     int64_t *tab = cost + (int64_t)c * rows * pitch;
     int16_t *dtab = dec + (int64_t)c * rows * pitch;
-    for_windows(M, blockDim.x, 0, 0, 1, threadIdx.x, R, [&](const Window &wn, int tile) {
+    Window wn{(int)blockDim.x, 0, 0, 0, false, (int)threadIdx.x, 0, 0};
+    for_passes(wn, M, INT_MAX, R, [&](const Window &wn, int tile) {
         if (cw.narrow(0))
             triangle_body<Narrow>(r, cw, L, M, pitch, tile, wn, tab, dtab, lds);
         else
             triangle_body<Wide>(r, cw, L, M, pitch, tile, wn, tab, dtab, lds);
-        return true;
     });
 }
 
@@ -986,7 +968,6 @@ __device__ __forceinline__ void with_key(const ChainWork &cw, int R, int C, F &&
 // (kAllTiles) or those inside the 16 x 16 diagonal blocks (kDiagonalBlocks); or, of
 // the blocks (I, I + delta), the tiles a + b = step (kBlockEdges), a groups above
 // the block's last and b right of its first.
-enum TileSet { kAllTiles, kDiagonalBlocks, kBlockEdges };
 struct TileSteps {
     TileSet set;
     int groups, delta;
@@ -1019,15 +1000,39 @@ struct TileSteps {
     }
 };
 
-// One step: the first n_tiles * n_v workgroups finish a window of a tile each,
-// the others take the inner splits of the next step's tiles, which read tiles
-// of the steps before this one only: so that the products, most of the work,
-// run beside the short dependent part.
-template <bool INNER, bool EDGE>
+// One launch of a run of tile steps: step `front` is the one whose first window
+// is finished.  Its workgroups for one chain, in order:
+//   tiles * windows        a window of a tile of step `front` each; of a chain
+//                          whose windows lie apart: window v of step front - v
+//   next * chunks          the inner splits of a tile of step front + 1 at the
+//                          budgets of `chunks` workgroups (not for those chains)
+// and for chains whose windows lie apart
+//   more * apart           the tiles that window v's step has more than `front`
+//   apart_next * apart_chunks * apart   the inner splits of the step after each
+//                          window's.
+// So the order of chains whose windows overlap, the usual ones, is not
+// stretched by the others'.
+struct TileLaunch {
+    TileSteps steps;
+    int front;
+    int first, last;  // the steps finished in this run
+    int inner_from;   // steps from here on get inner splits
+    int W, passes;    // budgets of a pass, passes in turn (where there is one window)
+    int halo;         // largest reach of chains with overlapping windows (-1: no chain; INT_MAX: one window)
+    int tiles, windows, next, chunks;
+    int more, apart, apart_passes, apart_next, apart_chunks;
+    int copy_W, copy_halo;  // overlapping windows that will read the inner results (copy_W = 0: none)
+    int n_kw;               // waves that share the inner splits of the same budgets
+};
+
+// A workgroup either finishes a window of a tile or takes the inner splits of a
+// tile of the step that follows, which read tiles of the steps before this one
+// only: so that the products, most of the work, run beside the short dependent
+// part.  INNER: some step finished has inner splits; WINDOWS: a tile's budgets are
+// cut into windows.
+template <bool INNER, bool EDGE, bool WINDOWS>
 __global__ __launch_bounds__(kTileMaxWaves * 64, 3) void tile_kernel(const int64_t *__restrict__ params, int L, int M,
-                                                                  int64_t pitch, int64_t rows, TileSteps steps,
-                                                                  int step, int n_tiles, int W, int overlap, int n_v,
-                                                                  int next_W, int next_overlap, int n_kw,
+                                                                  int64_t pitch, int64_t rows, TileLaunch tl,
                                                                   int64_t *__restrict__ cost,
                                                                   int16_t *__restrict__ dec, Work w)
 {
@@ -1036,114 +1041,203 @@ __global__ __launch_bounds__(kTileMaxWaves * 64, 3) void tile_kernel(const int64
     const ChainRows r = chain_rows(params, w, L, c);
     const ChainWork cw = chain_work(w, L, rows, pitch, c);
     int64_t *tab = cost + (int64_t)c * rows * pitch;
+    const int reach = WINDOWS ? cw.reach() : 0;  // here, beside the other scalars: a read further down waits alone
+    int v = 0, i, chunk = 0;
+    bool finishes = true, apart_only = false;
+    int b = blockIdx.x;
+    const int windows = WINDOWS ? tl.windows : 1;
+    if (b < tl.tiles * windows) {
+        v = WINDOWS ? b / tl.tiles : 0;
+        i = b - v * tl.tiles;
+    } else if ((b -= tl.tiles * windows) < tl.next * tl.chunks || !WINDOWS) {
+        finishes = false;
+        chunk = b / tl.next;
+        i = b - chunk * tl.next;
+    } else {
+        apart_only = true;
+        b -= tl.next * tl.chunks;
+        finishes = b < tl.more * tl.apart;
+        if (finishes) {
+            v = b / tl.more;
+            i = b - v * tl.more + tl.tiles;
+        } else {
+            b -= tl.more * tl.apart;
+            const int q = b / tl.apart_next;
+            i = b - q * tl.apart_next;
+            v = q / tl.apart_chunks;
+            chunk = q - v * tl.apart_chunks;
+        }
+    }
+    const bool apart = WINDOWS && reach > tl.halo;
+    const int step = tl.front - (apart ? v : 0) + (finishes ? 0 : 1);
+    if (step < (finishes ? tl.first : tl.inner_from) || step > tl.last || i >= tl.steps.count(step) ||
+        v >= (apart ? tl.apart : windows) || (apart_only ? !apart : apart && !finishes))
+        return;
     int R, C;
-    if ((int)blockIdx.x < n_tiles * n_v) {
-        const int v = blockIdx.x / n_tiles;
-        steps.at(step, blockIdx.x - v * n_tiles, R, C);
-        if (C >= steps.groups || (int)threadIdx.x >= W)
+    tl.steps.at(step, i, R, C);
+    if (C >= tl.steps.groups)
+        return;
+    const int span = tl.W * tl.apart_passes;  // budgets of a window that lies apart
+    if (finishes) {
+        if ((int)threadIdx.x >= tl.W)
             return;
         int16_t *dtab = dec + (int64_t)c * rows * pitch;
+        const bool has_inner = INNER && (EDGE || step >= kInnerLevel);
+        Window wn{tl.W, tl.halo, v * (apart ? span : tl.W - tl.halo), 0, apart && v > 0, (int)threadIdx.x, 0, 0};
+        if (v > 0)
+            wn.from = wn.w0 + (apart ? 0 : tl.halo);
         with_key(cw, R, C, [&](auto key, int S) {
-            for_windows(M, W, overlap, v, n_v, threadIdx.x, R, [&](const Window &wn, int tile) {
-                return tile_finish<decltype(key), INNER>(r, cw, L, M, pitch, tile, tile - R + C, S, wn, tab, dtab, lds);
+            for_passes(wn, M, apart ? tl.apart_passes : tl.passes, R, [&](const Window &wn, int tile) {
+                tile_finish<decltype(key), INNER>(r, cw, L, M, pitch, tile, tile - R + C, S, has_inner, wn, tab, dtab,
+                                                  lds);
             });
         });
     } else {
-        const int b = blockIdx.x - n_tiles * n_v;
-        const int n_next = steps.count(step + 1), chunk = b / n_next;
-        steps.at(step + 1, b - chunk * n_next, R, C);
-        if (C >= steps.groups)
-            return;
-        const int Wi = blockDim.x / n_kw;
+        const int Wi = blockDim.x / tl.n_kw;
         const int kw = __builtin_amdgcn_readfirstlane(threadIdx.x / Wi);
         const int at = threadIdx.x - kw * Wi;
-        int64_t *halo = next_W > 0 ? halo_of(cw, R, C - R) : nullptr;
+        int m = chunk * Wi + at;
+        if (apart)  // a wave past the window's budgets is idle, like one past M
+            m = m < span ? v * span + m : M + 1;
+        int64_t *halo = !apart && tl.copy_W > 0 ? halo_of(cw, R, C - R) : nullptr;
         with_key(cw, R, C, [&](auto key, int S) {
-            tile_inner<decltype(key), EDGE>(r, cw, L, M, pitch, R, C, S, chunk * Wi + at, at, Wi, n_kw, kw, tab, halo,
-                                            halo_pitch_of(cw), next_W, next_overlap, lds);
+            tile_inner<decltype(key), EDGE>(r, cw, L, M, pitch, R, C, S, m, at, Wi, tl.n_kw, kw, tab, halo,
+                                            halo_pitch_of(cw), tl.copy_W, tl.copy_halo, lds);
         });
     }
 }
 
 }  // namespace
 
-// Windows of a tile-diagonal of `tiles` tiles over all chains: W budgets of
-// one pass of a tile's workgroup, n_v workgroups per tile, `halo` budgets
-// apart from W.  Launches of few tiles take overlapping windows, small ones
-// where the budgets are few (sizes, and with them the halo needed, grow with
-// the budgets); from 128 tiles on the chip is full without them, and a
-// workgroup of four waves walks its tile's windows in turn (measured on
-// MI355X, against overlapping windows: ten chains of L = 101, M = 500 0.77 ->
-// 0.65 ms, 32 of L = 64, M = 640 0.81 -> 0.64 ms; one of L = 100, M = 1000, with
-// one workgroup of 16 waves per tile 0.49 -> 0.32 ms).
-struct TileWindows {
-    int W, halo, n_v;
+// Windows of a step of `tiles` tiles over all chains.  Launches of few tiles
+// cut the budgets, into small windows where they are few (sizes, and with them
+// the reach, grow with the budgets); from 128 tiles on the chip is full
+// without, and a workgroup of four waves walks its tile's budgets in turn
+// (measured on MI355X, against overlapping windows: ten chains of L = 101, M = 500
+// 0.77 -> 0.65 ms, 32 of L = 64, M = 640 0.81 -> 0.64 ms; one of L = 100, M = 1000,
+// with one workgroup of 16 waves per tile 0.49 -> 0.32 ms).
+struct WindowSize {
+    int W, halo;
 };
-static TileWindows tile_windows(const Tables &tb, int64_t tiles)
+constexpr WindowSize kWindowSizes[] = {{320, 128}, {512, 192}, {640, 256}};
+constexpr bool halos_fit()
+{
+    for (const WindowSize &s : kWindowSizes)
+        if (s.W % 64 || s.halo % 64 || s.W > 64 * kTileMaxWaves || 3 * s.halo > 2 * (s.W - s.halo))
+            return false;
+    return true;
+}
+static_assert(halos_fit(), "whole waves, and places for the halos (halo_pitch_of)");
+
+static void tile_windows(const Tables &tb, int64_t tiles, TileLaunch &tl)
 {
     const int chunks = (tb.M + 64) / 64;  // of 64 budgets
-    TileWindows tw;
+    tl.passes = tl.windows = tl.apart = tl.apart_passes = 1;
+    tl.halo = INT_MAX;
     if (tiles >= 128) {
-        const int passes = (chunks + 3) / 4;
-        tw.W = 64 * ((chunks + passes - 1) / passes);
-    } else {
-        tw.W = chunks <= 5 ? 64 * chunks : chunks < 12 ? 320 : chunks < 48 ? 512 : 640;
+        tl.passes = (chunks + 3) / 4;
+        tl.W = 64 * ((chunks + tl.passes - 1) / tl.passes);
+        return;
     }
-    tw.halo = tw.W == 320 ? 128 : tw.W == 512 ? 192 : 256;
+    if (chunks <= 5) {
+        tl.W = 64 * chunks;
+        return;
+    }
+    const WindowSize size = kWindowSizes[chunks < 12 ? 0 : chunks < 48 ? 1 : 2];
+    tl.W = size.W;
     // the workspace has a place for the halos' inner results from two blocks on
-    const bool overlap = tiles < 128 && tb.M >= tw.W && tb.L > kBlock;
-    tw.n_v = overlap ? (tb.M - tw.halo) / (tw.W - tw.halo) + 1 : 1;
-    return tw;
+    tl.halo = -1;
+    if (tb.L > kBlock) {
+        tl.halo = size.halo;
+        tl.windows = max(0, tb.M - size.halo) / (size.W - size.halo) + 1;
+    }
+    const int n = tb.M / size.W + 1;
+    tl.apart_passes = tl.steps.set == kBlockEdges && n > 2 ? 2 : 1;
+    tl.apart = (n + tl.apart_passes - 1) / tl.apart_passes;
+    tl.windows = max(tl.windows, tl.apart);
 }
 
-static void launch_step(const TileSteps &steps, int step, hipStream_t stream, const Tables &tb, const Work &w)
+TileRun::TileRun(const Tables &tables, TileSet set, int delta)
+    : tb(tables), set_(set), delta_(delta), groups_((tables.L + kG - 1) / kG)
 {
-    const bool edge = steps.set == kBlockEdges;
-    const int chunks = (tb.M + 64) / 64;  // of 64 budgets
-    // the edges begin with a launch of inner splits alone
-    const int n_tiles = step >= 0 ? steps.count(step) : 0, n_next = steps.count(step + 1);
-    const TileWindows tw = tile_windows(tb, (int64_t)n_tiles * tb.n_chains);
-    // how the next launch reads the inner results this one leaves
-    const TileWindows next = tile_windows(tb, (int64_t)n_next * tb.n_chains);
-    const int n_inner = n_next <= 0 ? 0 : edge ? 1 : max(0, kG * (step + 1) - 3 * kG + 1);
-    int waves = n_tiles > 0 ? tw.W / 64 : min(chunks, 4), n_kw = 1, inner_wgs = 0;
-    if (n_inner > 0) {
+    front_ = first_ = set == kBlockEdges ? -1 : 0;
+    last_ = set == kAllTiles ? groups_ - 1 : set == kDiagonalBlocks ? min(groups_, kPerBlock) - 1 : 2 * kPerBlock - 2;
+}
+
+int TileRun::step() const { return front_ <= last_ ? front_ : -1; }
+
+bool TileRun::more() const { return front_ < last_ + n_apart_; }
+
+void TileRun::launch(hipStream_t stream, const Work &w)
+{
+    if (set_ != kBlockEdges && front_ == 0) {
+        const int W = 64 * min((tb.M + 64) / 64, 8);
+        triangle_kernel<<<dim3(groups_, tb.n_chains), W, 2 * kG * sizeof(int64_t) * W, stream>>>(
+            tb.params, tb.L, tb.M, tb.pitch, tb.rows, tb.cost, tb.dec, w);
+        first_ = ++front_;
+        return;
+    }
+    TileLaunch tl;
+    tl.steps = TileSteps{set_, groups_, delta_};
+    const bool edge = set_ == kBlockEdges;
+    // windows of one size through a run; where a step's were all in one launch,
+    // the next one may begin a new run
+    if (n_apart_ == 1 && !edge)
+        first_ = front_;
+    tile_windows(tb, (int64_t)tl.steps.count(edge ? kPerBlock - 1 : first_) * tb.n_chains, tl);
+    n_apart_ = tl.apart;
+    TileLaunch next = tl;
+    if (n_apart_ == 1 && !edge && front_ < last_)
+        tile_windows(tb, (int64_t)tl.steps.count(front_ + 1) * tb.n_chains, next);
+    tl.copy_W = next.windows > 1 && next.halo > 0 ? next.W : 0;
+    tl.copy_halo = next.halo;
+    tl.front = front_;
+    tl.first = max(first_, 0);
+    tl.last = last_;
+    // the run before left those of this one's first step
+    tl.inner_from = edge ? 0 : max(kInnerLevel, first_ + 1);
+    auto finished = [&](int step) { return step >= tl.first && step <= last_ ? tl.steps.count(step) : 0; };
+    auto inner = [&](int step) { return step >= tl.inner_from && step <= last_ ? tl.steps.count(step) : 0; };
+    tl.tiles = finished(front_);
+    tl.next = inner(front_ + 1);
+    tl.more = tl.apart_next = 0;
+    if (tl.halo < INT_MAX)
+        for (int v = 0; v < tl.apart; ++v) {
+            tl.more = max(tl.more, finished(front_ - v) - tl.tiles);
+            tl.apart_next = max(tl.apart_next, inner(front_ + 1 - v));
+        }
+    const int chunks = (tb.M + 64) / 64;
+    const bool finishes = tl.tiles + tl.more > 0;
+    int waves = finishes ? tl.W / 64 : min(chunks, 4);
+    tl.n_kw = 1;
+    tl.chunks = tl.apart_chunks = 0;
+    if (tl.next + tl.apart_next > 0) {
         // waves of the inner splits: about 1024, at least 4 splits each
         // (measured: 512 and 2048 lose 5% at L = 339, M = 500 and ten chains of
         // L = 101)
-        const int64_t units = (int64_t)n_next * chunks * tb.n_chains;
+        const int step = min(front_ + 1, last_), most = edge ? 1 : kG * step - 3 * kG + 1;
+        const int64_t units = (int64_t)tl.steps.count(step) * chunks * tb.n_chains;
         auto rounded = [&](int kw) { return (waves + kw - 1) / kw * kw; };
-        while (n_kw < 8 && units * n_kw < 1024 && n_inner >= 8 * n_kw && rounded(2 * n_kw) <= kTileMaxWaves)
-            n_kw *= 2;
-        waves = rounded(n_kw);
-        const int bw = waves / n_kw;
-        inner_wgs = (chunks + bw - 1) / bw * n_next;
+        while (tl.n_kw < 8 && units * tl.n_kw < 1024 && most >= 8 * tl.n_kw && rounded(2 * tl.n_kw) <= kTileMaxWaves)
+            tl.n_kw *= 2;
+        waves = rounded(tl.n_kw);
+        const int bw = waves / tl.n_kw;
+        tl.chunks = (chunks + bw - 1) / bw;
+        tl.apart_chunks = (tl.W / 64 * tl.apart_passes + bw - 1) / bw;
     }
     const int threads = 64 * waves;
-    const size_t lds = max(2 * kG * sizeof(int64_t) * (size_t)(n_tiles > 0 ? tw.W : 0),
-                           n_kw > 1 ? kG * kG * sizeof(int64_t) * (size_t)(threads / n_kw) : 0);
-    const auto kernel = edge ? tile_kernel<true, true>
-                             : step >= kInnerLevel ? tile_kernel<true, false> : tile_kernel<false, false>;
-    kernel<<<dim3(n_tiles * tw.n_v + inner_wgs, tb.n_chains), threads, lds, stream>>>(
-        tb.params, tb.L, tb.M, tb.pitch, tb.rows, steps, step, n_tiles, tw.W, tw.halo, tw.n_v,
-        next.n_v > 1 ? next.W : 0, next.halo, n_kw, tb.cost, tb.dec, w);
-}
-
-void launch_tile_edges(int step, int delta, hipStream_t stream, const Tables &tb, const Work &w)
-{
-    launch_step(TileSteps{kBlockEdges, (tb.L + kG - 1) / kG, delta}, step, stream, tb, w);
-}
-
-void launch_tiles(int level, bool in_blocks, hipStream_t stream, const Tables &tb, const Work &w)
-{
-    const int groups = (tb.L + kG - 1) / kG;
-    if (level == 0) {
-        const int W = 64 * min((tb.M + 64) / 64, 8);
-        triangle_kernel<<<dim3(groups, tb.n_chains), W, 2 * kG * sizeof(int64_t) * W, stream>>>(
-            tb.params, tb.L, tb.M, tb.pitch, tb.rows, tb.cost, tb.dec, w);
-        return;
-    }
-    launch_step(TileSteps{in_blocks ? kDiagonalBlocks : kAllTiles, groups, 0}, level, stream, tb, w);
+    const size_t lds = max(2 * kG * sizeof(int64_t) * (size_t)(finishes ? tl.W : 0),
+                           tl.n_kw > 1 ? kG * kG * sizeof(int64_t) * (size_t)(threads / tl.n_kw) : 0);
+    const int wgs = tl.tiles * tl.windows + tl.next * tl.chunks + tl.more * tl.apart +
+                    tl.apart_next * tl.apart_chunks * tl.apart;
+    const bool windows = tl.halo < INT_MAX, has_inner = front_ >= kInnerLevel;
+    const auto kernel = edge ? (windows ? tile_kernel<true, true, true> : tile_kernel<true, true, false>)
+                        : has_inner ? (windows ? tile_kernel<true, false, true> : tile_kernel<true, false, false>)
+                                    : (windows ? tile_kernel<false, false, true> : tile_kernel<false, false, false>);
+    if (wgs > 0)
+        kernel<<<dim3(wgs, tb.n_chains), threads, lds, stream>>>(tb.params, tb.L, tb.M, tb.pitch, tb.rows, tl, tb.cost,
+                                                                 tb.dec, w);
+    ++front_;
 }
 
 }  // namespace rotor
