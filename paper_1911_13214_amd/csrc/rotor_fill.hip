@@ -88,23 +88,25 @@
 namespace rotor {
 namespace {
 
-// The automatic schedule streams small tables.  By tiles, up to 1.8e10 split
-// candidates for one chain (8e9 from 1024 budgets on) and 7e9 over a batch;
-// measured on MI355X, blocked (edges by tiles) against streamed: L = 339, M = 500
-// (3e9) 3.7 / 1.9 ms; L = 500, M = 500 (1e10) 6.7 / 5.2 ms; L = 1001, M = 100 (2e10)
-// 11.1 / 9.7 ms; L = 500, M = 1000 (2e10) 7.5 / 8.8 ms; L = 200, M = 4500 (6e9)
-// 2.6 / 2.1 ms; L = 303, M = 2000 (9e9) 3.9 / 3.8 ms, on the 64-bit path 6.0 / 7.1 ms;
-// 32 chains of L = 64, M = 640 (9e8) 0.94 / 0.65 ms, 40 of L = 130, M = 700 (1e10)
-// 4.8 / 4.8 ms.  (256 chains of L = 64, M = 640, 7.2e9, stay blocked at 4.3 against
-// 3.8 ms: the breakdown by kernel classes of that workload is documented.)  The
-// tiles take 2 bytes of operands per candidate past the L2 (4 on the 64-bit
-// path), the blocked order's middle products a sixth of that.  By diagonals
-// (tiles_take), up to 2e9 for one chain (L = 250 at M = 500) and 4e8 for a batch.
-// Any single chain with fewer than 64 budgets is streamed: they leave most lanes
-// of the blocked kernels' 64-budget chunks idle.
+// The automatic schedule streams small tables.  By tiles (tiles_take), up to
+// 1.8e10 split candidates for one chain (8e9 from 1024 budgets on) and 8e9 over a
+// batch; measured on MI355X, streamed against blocked (edges by
+// tiles), values of 4 bytes, then of 8: L = 1001, M = 100 (1.7e10) 9.4 / 10.8 ms,
+// 16.2 / 16.3; L = 800, M = 180 (1.5e10) 7.6 / 8.7, 13.1 / 13.0; L = 600, M = 400
+// (1.44e10) 7.3 / 7.7, 12.9 / 11.3; L = 500, M = 700 (1.46e10) 7.0 / 7.0, 12.4 / 10.5;
+// L = 450, M = 900 (1.4e10) 6.0 / 6.3, 11.5 / 9.6; L = 300, M = 1700 (8e9) 3.4 / 3.9,
+// 6.1 / 5.8; L = 500, M = 1000 (2e10) 8.8 / 7.5; batches: 128 chains of L = 64,
+// M = 640 (4e9) 2.0 / 2.2 ms, 256 of them (7e9) 3.8 / 3.9, 300 (8.4e9) 4.4 / 4.6, 30 of
+// L = 130, M = 700 (8e9) 3.8 / 3.9, 25 of L = 150, M = 600 (8.4e9) 4.3 / 4.2, 64 of
+// L = 130, M = 400 (9e9) 4.9 / 4.6, 40 of L = 130, M = 700 (1e10) 4.9 / 4.7.  The tiles take 2
+// bytes of operands per candidate (4 on the 64-bit path), the blocked order's
+// middle products a sixth of that.  By diagonals, up to 2e9 for one chain
+// (L = 250 at M = 500) and 4e8 for a batch.  Any single chain with fewer than 64
+// budgets is streamed: they leave most lanes of the blocked kernels' 64-budget
+// chunks idle.
 constexpr uint64_t kTileMaxCandidates1 = 18000000000ull;
 constexpr uint64_t kTileMaxCandidatesWindows = 8000000000ull;
-constexpr uint64_t kTileMaxCandidatesN = 7000000000ull;
+constexpr uint64_t kTileMaxCandidatesN = 8000000000ull;
 constexpr uint64_t kStreamMaxCandidates1 = 2000000000ull;
 constexpr uint64_t kStreamMaxCandidatesN = 400000000ull;
 constexpr int kStreamBelowBudgets = 64;

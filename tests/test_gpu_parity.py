@@ -347,21 +347,23 @@ def test_reconstruct_status_codes():
     assert status[0].item() == rotor.ROTOR_ECORRUPT
 
 
-@pytest.mark.parametrize("cfg", [2, 3, 4])
-def test_timed_solve_matches_and_counts_the_work(cfg):
-    # random L=50 and ResNet-like L=100 take the streamed order, the batch
-    # workload the blocked one (middle and edge classes)
+@pytest.mark.parametrize("cfg,n", [(2, 1), (3, 1), (4, 256), (4, 320)])
+def test_timed_solve_matches_and_counts_the_work(cfg, n):
+    # random L=50, ResNet-like L=100 and the batch workload take the streamed
+    # order, a larger batch the blocked one (middle and edge classes)
     import torch
 
     from paper_1911_13214_amd import rotor
-    params, L, M, n, _ = chaingen.config(cfg)
-    say(f"timed cfg {cfg}")
+    params, L, M, n_cfg, _ = chaingen.config(cfg)
+    if n > n_cfg:
+        params = np.concatenate([params, params[:n - n_cfg]])
+    say(f"timed cfg {cfg} n={n}")
     d_params, cost, dec = solve_on_gpu(params, M)
     c2, d2 = rotor.alloc_tables(n, L, M)
     stats = rotor.rotor_solve_timed(d_params, n, L, M, c2, d2, rotor.alloc_workspace(n, L, M))
     torch.cuda.synchronize()
     assert torch.equal(cost[..., :M + 1], c2[..., :M + 1]) and torch.equal(dec[..., :M + 1], d2[..., :M + 1])
-    blocked = cfg == 4
+    blocked = n == 320
     assert (stats["middle"]["launches"] > 0) == blocked and (stats["edge"]["launches"] > 0) == blocked
     W = M + 1
     assert sum(s["split_candidates"] for s in stats.values()) == (L ** 3 - L) // 6 * W * n
