@@ -89,8 +89,8 @@ namespace rotor {
 namespace {
 
 // The automatic schedule streams small tables.  By tiles (tiles_take), up to
-// 1.8e10 split candidates for one chain (8e9 from 1024 budgets on) and 8e9 over a
-// batch; measured on MI355X, streamed against blocked (edges by
+// 1.45e10 split candidates for one chain (1.8e10 below 256 budgets, 8e9 from 1024
+// on) and 8e9 over a batch; measured on MI355X, streamed against blocked (edges by
 // tiles), values of 4 bytes, then of 8: L = 1001, M = 100 (1.7e10) 9.4 / 10.8 ms,
 // 16.2 / 16.3; L = 800, M = 180 (1.5e10) 7.6 / 8.7, 13.1 / 13.0; L = 600, M = 400
 // (1.44e10) 7.3 / 7.7, 12.9 / 11.3; L = 500, M = 700 (1.46e10) 7.0 / 7.0, 12.4 / 10.5;
@@ -104,7 +104,8 @@ namespace {
 // (L = 250 at M = 500) and 4e8 for a batch.  Any single chain with fewer than 64
 // budgets is streamed: they leave most lanes of the blocked kernels' 64-budget
 // chunks idle.
-constexpr uint64_t kTileMaxCandidates1 = 18000000000ull;
+constexpr uint64_t kTileMaxCandidatesFew = 18000000000ull;
+constexpr uint64_t kTileMaxCandidates1 = 14500000000ull;
 constexpr uint64_t kTileMaxCandidatesWindows = 8000000000ull;
 constexpr uint64_t kTileMaxCandidatesN = 8000000000ull;
 constexpr uint64_t kStreamMaxCandidates1 = 2000000000ull;
@@ -2097,6 +2098,7 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
     const bool tiles = tiles_take(L, tb.M);
     const uint64_t stream_max = nc > 1 ? (tiles ? kTileMaxCandidatesN : kStreamMaxCandidatesN)
                                 : !tiles ? kStreamMaxCandidates1
+                                : tb.M < 256  ? kTileMaxCandidatesFew
                                 : tb.M < 1024 ? kTileMaxCandidates1
                                               : kTileMaxCandidatesWindows;
     const bool streamed =
