@@ -153,6 +153,10 @@ constexpr int kTileEdgeWaves = 200;
 // 2.4 -> 6.3 ms; 16 chains of L = 64, M = 2047 1.4 -> 1.8, 1.6 -> 2.0; 256 of L = 35,
 // M = 1000 3.4 -> 2.7, 3.3 -> 2.7.
 constexpr int kTileEdgeBudgets = 1024, kTileEdgeBudgetsPerStage = 8;
+// Block-diagonals of so many blocks by tiles fill the chip by themselves: the next
+// one's inner products beside them lose (256 chains of L = 130, M = 1000 30.5 -> 32.3 ms,
+// 64 of L = 130, M = 400 4.6 -> 4.8).
+constexpr int kAloneBlocks = 256;
 constexpr int kSplitMinD = 16;  // diagonals from this length spread their splits over four waves
 
 // ---------------------------------------------------------------------------
@@ -2231,8 +2235,8 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
     // The inner middle range of block-diagonal delta + 1 (from delta + 1 = 3
     // on) reads only block-diagonals up to delta - 1: it runs on the
     // device's side stream beside the rim and the edges of delta, and its
-    // own rim follows them; only beside edges by rounds (the row edges of a
-    // batch lose: 4.95 -> 5.06 ms for 256 chains of L = 64).  An observer
+    // own rim follows them; not beside edges by rows (4.95 -> 5.06 ms for 256
+    // chains of L = 64) or by tiles of many blocks (kAloneBlocks).  An observer
     // sees the side stream's launches on that stream.
     bool overlap = side_stream && schedule != ROTOR_SCHEDULE_BLOCKED_SERIAL && nb >= 4;
     SideStream *side = nullptr;
@@ -2252,9 +2256,11 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
         for (int delta = 1; delta < nb; ++delta) {
             const uint64_t pairs = pairs_of(delta);
             const int span = (delta - 1) * kT + 1;
-            const bool rows = schedule == ROTOR_SCHEDULE_BLOCKED_ROWS ||
-                              (schedule != ROTOR_SCHEDULE_BLOCKED_ROUNDS &&
-                               row_edges((int64_t)(nb - delta) * tb.n_chains));
+            const int64_t blocks = (int64_t)(nb - delta) * tb.n_chains;
+            const bool rows = !tile_edges(delta) &&
+                              (schedule == ROTOR_SCHEDULE_BLOCKED_ROWS ||
+                               (schedule != ROTOR_SCHEDULE_BLOCKED_ROUNDS && row_edges(blocks)));
+            const bool alone = rows || (tile_edges(delta) && blocks >= kAloneBlocks);
             // the middle splits of every pair, and C_2 of the corner cell of
             // every block when the middle products finish the corners
             const int n_part = inner_done ? 1 : parts_of(delta);
@@ -2270,7 +2276,7 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
             // where they return at once
             if ((e = middle_general(delta, range, n_part, stream)) != hipSuccess)
                 return e;
-            const bool next_inner = overlap && !rows && delta + 1 < nb && delta + 1 >= 3;
+            const bool next_inner = overlap && !alone && delta + 1 < nb && delta + 1 >= 3;
             if (next_inner) {
                 // the inner splits of every pair of delta + 1: all but 2 kT
                 const int np = parts_of(delta + 1);
