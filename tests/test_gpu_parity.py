@@ -20,11 +20,11 @@ def say(msg):
     print(msg, flush=True)
 
 
-# the blocked fill with its edges by anti-diagonal rounds (the inner middle
-# products beside the previous edges, on the side stream) and by rows, the
-# blocked fill on one stream, and the streamed diagonals
-SCHEDULES = ["rounds", "rows", "serial", "diagonal"]
-EDGE_ORDERS = ["rounds", "rows", "serial"]
+# the blocked fill with its edges by tiles (at these sizes) and by anti-diagonal
+# rounds (both with the inner middle products beside the previous edges, on the
+# side stream), by rows, and by tiles on one stream; and the streamed tiles
+SCHEDULES = ["blocked", "rounds", "rows", "serial", "diagonal"]
+EDGE_ORDERS = ["blocked", "rounds", "rows", "serial"]
 _oracle_cache = {}
 
 
@@ -705,20 +705,22 @@ def test_orders_agree_on_a_table_beyond_4_gb():
     # compact copy, so row offsets pass 32 bits; the cost bound (~2.5e7)
     # leaves 7 bits of split field, so block-diagonals up to 8 take packed
     # middle keys and the later ones the (value, split) middle kernel.  The
-    # blocked and the streamed order share no kernel beyond the leaves and
-    # the in-block diagonals; every cell must agree, and 36-stage windows
-    # must equal the oracle's tables.
+    # blocked order with edges by rounds and the streamed one (by tiles) share
+    # no kernel, and the blocked order's own choice takes tiles for the last
+    # block-diagonals; every cell must agree, and 36-stage windows must equal
+    # the oracle's tables.
     import torch
     from paper_1911_13214_amd import rotor
     L, M = 1000, 4000
     p = chaingen.random_chains(1, L, seed=1000)
     assert (1 << 24) < cost_bound(p[0]) < (1 << 25)
     say(f"orders at scale L={L} M={M}")
-    _, c1, d1 = solve_on_gpu(p, M, schedule="blocked")
-    _, c2, d2 = solve_on_gpu(p, M, schedule="diagonal")
-    assert torch.equal(c1[..., :M + 1], c2[..., :M + 1]) and torch.equal(d1[..., :M + 1], d2[..., :M + 1])
-    del c2, d2
-    torch.cuda.empty_cache()
+    _, c1, d1 = solve_on_gpu(p, M, schedule="rounds")
+    for other in ("diagonal", "blocked"):
+        _, c2, d2 = solve_on_gpu(p, M, schedule=other)
+        assert torch.equal(c1[..., :M + 1], c2[..., :M + 1]) and torch.equal(d1[..., :M + 1], d2[..., :M + 1]), other
+        del c2, d2
+        torch.cuda.empty_cache()
     for a in (1, 483, 965):
         b = a + 35
         C, D = oracle_tables(np.ascontiguousarray(p[:, :, a - 1:b]), M)
@@ -780,7 +782,8 @@ def test_fill_replays_from_a_captured_graph():
         assert_same(params, M, cost, dec)
 
 
-def test_two_stream_fill_replays_from_a_captured_graph():
+@pytest.mark.parametrize("schedule", ["blocked", "rounds"])
+def test_two_stream_fill_replays_from_a_captured_graph(schedule):
     # the blocked order forks its inner middle products onto the library's
     # side stream and joins it back with events: under capture that is a
     # fork and a join of the graph, and every replay must rebuild the tables
@@ -788,19 +791,19 @@ def test_two_stream_fill_replays_from_a_captured_graph():
     from paper_1911_13214_amd import rotor
     L, M = 80, 300
     params = chaingen.random_chains(1, L, seed=808)
-    say(f"graph replay of the two-stream blocked fill L={L} M={M}")
+    say(f"graph replay of the two-stream blocked fill L={L} M={M} {schedule}")
     d_params = rotor.upload_params(params, M)
     cost, dec = rotor.alloc_tables(1, L, M)
     work = rotor.alloc_workspace(1, L, M)
     st = torch.cuda.Stream()
     st.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(st):
-        rotor.rotor_solve_schedule(d_params, 1, L, M, cost, dec, work, "rounds", st)
+        rotor.rotor_solve_schedule(d_params, 1, L, M, cost, dec, work, schedule, st)
     torch.cuda.synchronize()
     assert_same(params, M, cost, dec)
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph, stream=st):
-        rotor.rotor_solve_schedule(d_params, 1, L, M, cost, dec, work, "rounds", st)
+        rotor.rotor_solve_schedule(d_params, 1, L, M, cost, dec, work, schedule, st)
     torch.cuda.synchronize()
     for _ in range(3):
         cost.fill_(-7)
@@ -812,7 +815,8 @@ def test_two_stream_fill_replays_from_a_captured_graph():
         assert_same(params, M, cost, dec)
 
 
-def test_two_stream_fills_from_two_host_threads():
+@pytest.mark.parametrize("schedule", ["blocked", "rounds"])
+def test_two_stream_fills_from_two_host_threads(schedule):
     # solves from several host threads share the device's side stream: each
     # enqueues under the library's lock, and every table must come out whole
     import threading
@@ -820,7 +824,7 @@ def test_two_stream_fills_from_two_host_threads():
     from paper_1911_13214_amd import rotor
     L, M = 72, 260
     chains = [chaingen.random_chains(1, L, seed=900 + i) for i in range(2)]
-    say(f"two host threads, two-stream blocked fills L={L} M={M}")
+    say(f"two host threads, two-stream blocked fills L={L} M={M} {schedule}")
     bufs = []
     for p in chains:
         bufs.append((rotor.upload_params(p, M), *rotor.alloc_tables(1, L, M), rotor.alloc_workspace(1, L, M),
@@ -832,7 +836,7 @@ def test_two_stream_fills_from_two_host_threads():
         try:
             d_params, cost, dec, work, st = bufs[i]
             for _ in range(4):
-                rotor.rotor_solve_schedule(d_params, 1, L, M, cost, dec, work, "rounds", st)
+                rotor.rotor_solve_schedule(d_params, 1, L, M, cost, dec, work, schedule, st)
             st.synchronize()
         except Exception as e:  # reported in the main thread
             errors.append(e)

@@ -37,12 +37,20 @@ def _tables_both_ways(params, M):
 
 def test_noalloc_equals_rotor_solve_on_two_calls():
     from paper_1911_13214_amd import rotor
-    # 16 chains of L=64, M=640: the blocked fill order, about 90 MB of workspace;
-    # then one chain of L=50, M=500: the streamed order, about 2 MB
-    cases = [(chaingen.random_chains(16, 64, seed=901), 640), (chaingen.random_chains(1, 50, seed=902), 500)]
-    for params, M in cases:
+    # 16 chains of L=64, M=640: the streamed order by tiles, about 90 MB of workspace;
+    # 4 of L=64, M=2400: the blocked order, about 105 MB; then one chain of L=50, M=500:
+    # streamed, about 2 MB; and 10 of L=8, M=5000: streamed by diagonals
+    cases = [(chaingen.random_chains(16, 64, seed=901), 640, False),
+             (chaingen.random_chains(4, 64, seed=903), 2400, True),
+             (chaingen.random_chains(1, 50, seed=902), 500, False),
+             (chaingen.random_chains(10, 8, seed=904), 5000, False)]
+    for params, M, blocked in cases:
         n, _, L = params.shape
         need = rotor.rotor_workspace_bytes(n, L, M)
+        d_params = rotor.upload_params(params, M, "cuda")
+        stats = rotor.rotor_solve_timed(d_params, n, L, M, *rotor.alloc_tables(n, L, M, "cuda"),
+                                        rotor.alloc_workspace(n, L, M, "cuda"))
+        assert (stats["middle"]["launches"] > 0) == blocked  # the order is chosen by the sizes alone
         print(f"noalloc n={n} L={L} M={M} workspace {need} bytes", flush=True)
         assert need <= rotor.NOALLOC_WORK_BYTES
         c, d, rc, rd = _tables_both_ways(params, M)
