@@ -242,17 +242,19 @@ ROTOR_API int32_t rotor_solve_status(const void *d_work, uint64_t work_bytes, in
  *                            640 budgets or fewer), the splits that a tile
  *                            shares as register products; from M = 320 on,
  *                            for the shortest chains and where M > 24 L (from
- *                            M = 1024 on; from 512 on below 20 stages), one
- *                            launch per t - s over all pairs, the splits of a
- *                            pair spread over four waves from t - s = 16 on;
- *                            few launches, the fast order for small tables.
+ *                            M = 512 on, 1024 from 20 stages on, 5120 from 64
+ *                            on), one launch per t - s over all pairs, the
+ *                            splits of a pair spread over four waves from
+ *                            t - s = 16 on; few launches, the fast order for
+ *                            small tables.
  *   ROTOR_SCHEDULE_AUTO      DIAGONAL when the table has at most 1.45e10 split
  *                            candidates (L^3/6 (M+1)) for one chain with
  *                            M < 1024 (1.8e10 with M < 256), 8e9 for one with
- *                            more budgets, 8e9 summed over a batch (by tiles;
- *                            2e9 and 4e8 where it goes by t - s), or when one
- *                            chain has M < 63; BLOCKED otherwise (the order
- *                            rotor_solve uses).
+ *                            more budgets, 8e9 summed over a batch (3e9 with
+ *                            M >= 1024 and M > 24 L; by tiles; 2e9 and 4e8
+ *                            where it goes by t - s), or when one chain has
+ *                            M < 63; BLOCKED otherwise (the order rotor_solve
+ *                            uses).
  *   ROTOR_SCHEDULE_BLOCKED_ROWS, ROTOR_SCHEDULE_BLOCKED_ROUNDS
  *                            BLOCKED with the edges of every block-diagonal
  *                            by rows, or by anti-diagonals.

@@ -108,6 +108,11 @@ constexpr uint64_t kTileMaxCandidatesFew = 18000000000ull;
 constexpr uint64_t kTileMaxCandidates1 = 14500000000ull;
 constexpr uint64_t kTileMaxCandidatesWindows = 8000000000ull;
 constexpr uint64_t kTileMaxCandidatesN = 8000000000ull;
+// a batch of more than 24 budgets per stage (from 1024 on); sizes from half of
+// store-everything, streamed against blocked (edges by rounds or rows): 10 of L = 64,
+// M = 3000 (1.3e9) 1.1 / 1.3 ms, 8 of L = 80, M = 5000 (3.4e9) 2.5 / 2.3, 20 of L = 70,
+// M = 4000 (4.6e9) 3.9 / 3.3
+constexpr uint64_t kTileMaxCandidatesShortN = 3000000000ull;
 constexpr uint64_t kStreamMaxCandidates1 = 2000000000ull;
 constexpr uint64_t kStreamMaxCandidatesN = 400000000ull;
 constexpr int kStreamBelowBudgets = 64;
@@ -121,7 +126,10 @@ constexpr int kStreamBelowBudgets = 64;
 // 34 / 37; L = 12, M = 500 46 / 51, 37 / 50; L = 13, M = 500 58 / 56, 48 / 55; L = 20,
 // M = 500 70 / 86, 57 / 84; L = 20, M = 1000 79 / 87, 60 / 82; L = 20, M = 1500 96 / 87;
 // L = 24, M = 700 99 / 103; L = 32, M = 1500 136 / 135; L = 64, M = 1500 246 / 308,
-// 210 / 282; L = 100, M = 2400 0.44 / 0.86 ms, 0.35 / 0.62; L = 200, M = 4500 3.0 / 3.4.
+// 210 / 282; L = 100, M = 2400 0.44 / 0.86 ms, 0.35 / 0.62; L = 64, M = 5000 0.43 / 0.50,
+// 0.30 / 0.36; L = 150, M = 5000 1.7 / 2.5 (blocked), 1.4 / 2.3, and a tenth of
+// store-everything 1.9 / 2.7; L = 200, M = 5000 3.5 / 3.6 (blocked), 2.5 / 3.2; L = 50,
+// M = 3500 0.30 / 0.27, L = 150, M = 10000 3.3 / 3.2 (blocked).
 constexpr int kTileBudgetsPerStage = 24;
 bool tiles_take(int L, int M)
 {
@@ -130,7 +138,7 @@ bool tiles_take(int L, int M)
     const int groups = (L + kTileSide - 1) / kTileSide, launches = groups + (groups > 1 ? 1 : 0);
     if (launches > 1 && 8 * launches > 3 * L)
         return false;
-    return M < (L >= 20 ? 1024 : 512) || M <= kTileBudgetsPerStage * L;
+    return M < (L >= 64 ? 5120 : L >= 20 ? 1024 : 512) || M <= kTileBudgetsPerStage * L;
 }
 // Blocked edges by tiles (launch_fill), measured on MI355X against the rounds (rows
 // for batches): L = 500, M = 1000 (2e10) 9.0 -> 7.5 ms, L = 700, M = 500 (3e10)
@@ -2100,7 +2108,10 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
     // stages; the blocked fill would need 33 per sixteen.
     const uint64_t r_total = ((uint64_t)L * L * L / 6) * W * nc;
     const bool tiles = tiles_take(L, tb.M);
-    const uint64_t stream_max = nc > 1 ? (tiles ? kTileMaxCandidatesN : kStreamMaxCandidatesN)
+    const bool short_chains = tb.M >= 1024 && tb.M > kTileBudgetsPerStage * L;
+    const uint64_t stream_max = nc > 1 ? (!tiles         ? kStreamMaxCandidatesN
+                                          : short_chains ? kTileMaxCandidatesShortN
+                                                         : kTileMaxCandidatesN)
                                 : !tiles ? kStreamMaxCandidates1
                                 : tb.M < 256  ? kTileMaxCandidatesFew
                                 : tb.M < 1024 ? kTileMaxCandidates1

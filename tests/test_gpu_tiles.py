@@ -57,7 +57,7 @@ def test_tile_windows_change(n, L, M):
 # also where budgets in turn come before, and chains of one block, which have
 # no overlap
 @pytest.mark.parametrize("n,L,M", [(1, 8, 400), (1, 11, 511), (2, 16, 500), (3, 40, 330), (3, 30, 1023), (2, 61, 1464),
-                                   (12, 45, 600), (30, 22, 700)])
+                                   (12, 45, 600), (30, 22, 700), (2, 66, 5119)])
 def test_windows_apart_beside_overlapping_ones(n, L, M):
     p = chaingen.random_chains(n, L, seed=800 + L)
     p[::2, 2:] *= 40

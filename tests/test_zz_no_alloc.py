@@ -38,10 +38,10 @@ def _tables_both_ways(params, M):
 def test_noalloc_equals_rotor_solve_on_two_calls():
     from paper_1911_13214_amd import rotor
     # 16 chains of L=64, M=640: the streamed order by tiles, about 90 MB of workspace;
-    # 4 of L=64, M=2400: the blocked order, about 105 MB; then one chain of L=50, M=500:
+    # 4 of L=63, M=2600: the blocked order, about 100 MB; then one chain of L=50, M=500:
     # streamed, about 2 MB; and 10 of L=8, M=5000: streamed by diagonals
     cases = [(chaingen.random_chains(16, 64, seed=901), 640, False),
-             (chaingen.random_chains(4, 64, seed=903), 2400, True),
+             (chaingen.random_chains(4, 63, seed=903), 2600, True),
              (chaingen.random_chains(1, 50, seed=902), 500, False),
              (chaingen.random_chains(10, 8, seed=904), 5000, False)]
     for params, M, blocked in cases:
