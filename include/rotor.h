@@ -69,12 +69,11 @@
  * of rotor_solve_noalloc, one device array per device; and, for the blocked
  * fill, one side stream and two events per device (created by the first
  * solve on the device, kept until the process ends), on which part of each
- * middle product runs beside the edge rounds before it (edges by
- * anti-diagonal rounds, not by rows) and which the solve joins
- * back into `stream` before it returns (if the side stream cannot be
- * created, every launch goes to `stream`).  Solves hold a lock while they
- * enqueue; concurrent calls on distinct output buffers and workspaces are
- * independent.
+ * middle product runs beside the edges before it (by tiles of fewer than 256
+ * blocks, or by anti-diagonal rounds) and which the solve joins back into
+ * `stream` before it returns (if the side stream cannot be created, every
+ * launch goes to `stream`).  Solves hold a lock while they enqueue; concurrent
+ * calls on distinct output buffers and workspaces are independent.
  */
 #ifndef ROTOR_H
 #define ROTOR_H
@@ -191,8 +190,8 @@ ROTOR_API int32_t rotor_solve(const int64_t *d_params, int32_t n_chains, int32_t
  * the same fill and tables, with the workspace taken from a static device
  * array of ROTOR_NOALLOC_WORK_BYTES bytes per device instead of a caller
  * buffer, and every launch on `stream` (no side stream: the blocked fill's
- * middle products wait for the edges before them).  The caller still passes parameters and tables (as for
- * rotor_solve).  It calls no hipMalloc, hipFree or allocating library
+ * middle products wait for the edges before them).  The caller still passes
+ * parameters and tables (as for rotor_solve).  It calls no hipMalloc, hipFree or allocating library
  * routine.  Every call on one device shares that device's array, so calls
  * that overlap on one device (different streams, or host threads) race and
  * must be serialised by the caller; nothing left in the array by an earlier

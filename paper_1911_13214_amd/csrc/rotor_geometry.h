@@ -39,6 +39,11 @@ constexpr int64_t pitch_of(int64_t M) { return (M + 1 + 31) / 32 * 32; }
 // elements (128 bytes).
 constexpr int64_t half_pitch_of(int64_t pitch) { return (pitch + 63) / 64 * 64; }
 
+// Rows of that copy per chain: kBlock per stage, none in a single block (no
+// edges).  Fills by 4 x 4 tiles, which need no copy, keep results of budgets
+// that two windows compute there.
+constexpr int64_t half_rows_of(int L) { return L > kBlock ? (int64_t)L * kBlock : 0; }
+
 // Whether the batch sizes are within what the ABI accepts.
 constexpr bool sizes_ok(int32_t n_chains, int32_t L, int64_t M)
 {

@@ -36,8 +36,7 @@ WorkLayout work_layout(int n_chains, int L, int64_t pitch)
     wl.shift = align(wl.status + 4ull * nc);
     wl.shadow = align(wl.shift + 8ull * nc * (uint64_t)L);
     wl.half = align(wl.shadow + 4ull * nc * rows * (uint64_t)pitch);
-    const uint64_t half_rows = nb >= 2 ? (uint64_t)L * kBlock : 0;  // no edges in a single block
-    wl.total = align(wl.half + 2ull * nc * half_rows * (uint64_t)half_pitch_of(pitch));
+    wl.total = align(wl.half + 2ull * nc * (uint64_t)half_rows_of(L) * (uint64_t)half_pitch_of(pitch));
     return wl;
 }
 

@@ -485,10 +485,9 @@ __device__ inline bool tile_saturated(const ChainRows &r, const ChainWork &cw, i
 // Inner results at the budgets that a second window computes again (the first
 // halo of every window but the first) are kept twice: in the cost slots, which
 // the window that stores those cells overwrites, and for the three lower rows
-// in the workspace's 2-byte section, which the tiles have no other use for: 128
-// half_pitch bytes per tile row group (16 rows of the section per stage, so a
-// chain's tiles fit), half of them for each parity of its tile-diagonal.
-// Budgets come in waves of 64.
+// in the workspace's 2-byte section, which the tiles have no other use for: a
+// slice of 64 of its rows per row group, half of it for each parity of the
+// tile-diagonal.  Budgets come in waves of 64.
 __device__ inline int halo_place(int base, int W, int halo)
 {
     const int per = (W - halo) >> 6, own = halo >> 6;
@@ -499,7 +498,16 @@ constexpr int kHaloRows = (kG - 1) * kG;
 constexpr int kHaloSlice = kG * kT;  // rows of the 2-byte section per row group
 // places of a row's halos: room for halos of up to 2/3 of W - halo
 __device__ inline int64_t halo_pitch_of(const ChainWork &cw) { return cw.hpitch * 2 / 3 / 64 * 64; }
-static_assert(2 * kHaloRows * 2 * sizeof(int64_t) <= 3 * kHaloSlice * sizeof(int16_t), "halos of both parities in a slice");
+static_assert(2 * kHaloRows * 2 * sizeof(int64_t) <= 3 * kHaloSlice * sizeof(int16_t), "both parities in a slice");
+// the row groups of tiles off the diagonal are all but the last
+constexpr bool slices_fit()
+{
+    for (int L = kBlock + 1; L <= 8 * kBlock; ++L)  // both sides grow alike
+        if ((int64_t)((L + kG - 1) / kG - 1) * kHaloSlice > half_rows_of(L))
+            return false;
+    return true;
+}
+static_assert(slices_fit(), "a chain's slices in its part of the section");
 __device__ inline int64_t *halo_of(const ChainWork &cw, int R, int level)
 {
     return (int64_t *)(cw.half + (int64_t)R * (kHaloSlice * cw.hpitch)) +

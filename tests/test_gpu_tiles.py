@@ -73,6 +73,34 @@ def test_block_edges_apart_beside_overlapping_ones(n, L, M):
     check(p, M, "blocked")
 
 
+# a chain outside the domain (negative, huge and 32-bit sizes) among windows
+# that overlap and lie apart: its neighbours' tables are the oracle's
+@pytest.mark.parametrize("schedule", ["diagonal", "blocked"])
+def test_windows_beside_a_chain_out_of_the_domain(schedule):
+    import torch
+
+    from gpu_util import chain_tables
+    from paper_1911_13214_amd import rotor
+    L, M = 40, 700
+    p = chaingen.random_chains(4, L, seed=1250)
+    p[3, 2:] *= 40
+    p[1, chaingen.WA, 7], p[1, chaingen.WABAR, 12] = -9, 1 << 62
+    p[2, chaingen.WA, 20], p[2, chaingen.WABAR, 30], p[2, chaingen.UF, 9] = (1 << 32) + 3, -7, -100
+    print(f"domain L={L} M={M} {schedule}", flush=True)
+    d_params = torch.from_numpy(p).to("cuda")
+    cost, dec = rotor.alloc_tables(4, L, M)
+    work = rotor.alloc_workspace(4, L, M)
+    rotor.rotor_solve_schedule(d_params, 4, L, M, cost, dec, work, schedule)
+    torch.cuda.synchronize()
+    st, per = rotor.rotor_solve_status(work, 4, L, M)
+    assert st == rotor.ROTOR_EDOMAIN
+    assert per.tolist() == [rotor.ROTOR_OK, rotor.ROTOR_EDOMAIN, rotor.ROTOR_EDOMAIN, rotor.ROTOR_OK]
+    for c in (0, 3):
+        C, D = orc.solve(p[c], M)
+        gc, gd = chain_tables(cost, dec, c, L, M)
+        assert np.array_equal(gc, C) and np.array_equal(gd, D), c
+
+
 def limited(n, L, M, seed, share):
     """Chains whose sizes add up to M / share: a memory limit of that share."""
     p = chaingen.random_chains(n, L, seed=seed)
