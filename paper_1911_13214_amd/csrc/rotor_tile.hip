@@ -23,11 +23,12 @@
 // the tile's bottom row up, left to right in a row: a row's cells meet as X
 // in registers (same budget), and the rows above read them, shifted by the one w_a
 // their row is always shifted by, from LDS, with one barrier per row.
-// Measured on MI355X against one launch per t - s: L = 50, M = 500 202 -> 150 us,
-// L = 339, M = 500 5.7 -> 1.9 ms.  A launch is bound by the finishing wave's
+// Measured on MI355X against one launch per t - s: L = 50, M = 500 202 -> 156 us,
+// L = 339, M = 500 5.7 -> 2.0 ms.  A launch is bound by the finishing wave's
 // dependent loads and about 2,500 instructions (8 to 12 us) and, in the middle
-// levels of long chains, by the inner splits' operands, 2 bytes per candidate
-// past the L2 at 4.4 TB/s.
+// levels of long chains and in batches, by bytes: L = 1001, M = 100 reads 2.6 per
+// candidate past the L2 and moves 5.0 TB/s, 256 chains of L = 64, M = 640 4.9 TB/s
+// (a large copy 4.7).
 #include <climits>
 
 #include "rotor_paths.h"
