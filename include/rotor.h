@@ -231,8 +231,9 @@ ROTOR_API int32_t rotor_solve_status(const void *d_work, uint64_t work_bytes, in
  *                            large against the budgets) in tables of up to
  *                            3e10 candidates, chains of up to 13 blocks and
  *                            for the last block-diagonals of larger ones, if
- *                            M < 1024, M <= 8 L, or M < 2048 and M <= 24 L;
- *                            else by rows (16 launches) when a block-diagonal
+ *                            M < 1024, or M <= 8 L, or M < 2048 and M <= 24 L
+ *                            (batches from M = 1024 on: and at least 256 blocks
+ *                            in the first block-diagonal); else by rows (16 launches) when a block-diagonal
  *                            holds at least 256 blocks over all chains, else
  *                            by anti-diagonals (30 short launches); the fast
  *                            order for large tables.
@@ -249,11 +250,11 @@ ROTOR_API int32_t rotor_solve_status(const void *d_work, uint64_t work_bytes, in
  *   ROTOR_SCHEDULE_AUTO      DIAGONAL when the table has at most 1.45e10 split
  *                            candidates (L^3/6 (M+1)) for one chain with
  *                            M < 1024 (1.8e10 with M < 256), 8e9 for one with
- *                            more budgets, 8e9 summed over a batch (3e9 with
- *                            M >= 1024 and M > 24 L; by tiles; 2e9 and 4e8
- *                            where it goes by t - s), or when one chain has
- *                            M < 63; BLOCKED otherwise (the order rotor_solve
- *                            uses).
+ *                            more budgets, 8e9 summed over a batch (7e9 with
+ *                            L > 128, 3e9 with M >= 1024 and M > 24 L; by
+ *                            tiles; 2e9 and 4e8 where it goes by t - s), or
+ *                            when one chain has M < 63; BLOCKED otherwise (the
+ *                            order rotor_solve uses).
  *   ROTOR_SCHEDULE_BLOCKED_ROWS, ROTOR_SCHEDULE_BLOCKED_ROUNDS
  *                            BLOCKED with the edges of every block-diagonal
  *                            by rows, or by anti-diagonals.

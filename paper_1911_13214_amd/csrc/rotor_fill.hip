@@ -90,7 +90,7 @@ namespace {
 
 // The automatic schedule streams small tables.  By tiles (tiles_take), up to
 // 1.45e10 split candidates for one chain (1.8e10 below 256 budgets, 8e9 from 1024
-// on) and 8e9 over a batch; measured on MI355X, streamed against blocked (edges by
+// on) and 8e9 over a batch (7e9 of chains of more than 128 stages); measured on MI355X, streamed against blocked (edges by
 // tiles), values of 4 bytes, then of 8: L = 1001, M = 100 (1.7e10) 9.4 / 10.8 ms,
 // 16.2 / 16.3; L = 800, M = 180 (1.5e10) 7.6 / 8.7, 13.1 / 13.0; L = 600, M = 400
 // (1.44e10) 7.3 / 7.7, 12.9 / 11.3; L = 500, M = 700 (1.46e10) 7.0 / 7.0, 12.4 / 10.5;
@@ -108,6 +108,10 @@ constexpr uint64_t kTileMaxCandidatesFew = 18000000000ull;
 constexpr uint64_t kTileMaxCandidates1 = 14500000000ull;
 constexpr uint64_t kTileMaxCandidatesWindows = 8000000000ull;
 constexpr uint64_t kTileMaxCandidatesN = 8000000000ull;
+// a batch of longer chains, between the crossovers of its 4- and its 8-byte values:
+// 8 of L = 208, M = 600 (7.2e9) 3.5 / 3.8 ms, 6.4 / 5.4; 4 of L = 250, M = 600 (6.2e9)
+// 2.9 / 3.5, 5.5 / 5.3
+constexpr uint64_t kTileMaxCandidatesLongN = 7000000000ull;
 // a batch of more than 24 budgets per stage (from 1024 on); sizes from half of
 // store-everything, streamed against blocked (edges by rounds or rows): 10 of L = 64,
 // M = 3000 (1.3e9) 1.1 / 1.3 ms, 8 of L = 80, M = 5000 (3.4e9) 2.5 / 2.3, 20 of L = 70,
@@ -159,7 +163,10 @@ constexpr int kTileEdgeWaves = 200;
 // M = 1500 3.9 -> 2.9 and 4.0 -> 3.8 ms, M = 2000 4.0 -> 3.1, 4.1 -> 4.1; L = 300, M = 2400
 // 5.3 -> 4.5, 5.7 -> 5.8; L = 150, M = 5000 2.5 -> 3.3, 2.7 -> 3.6; L = 100, M = 20000
 // 2.4 -> 6.3 ms; 16 chains of L = 64, M = 2047 1.4 -> 1.8, 1.6 -> 2.0; 256 of L = 35,
-// M = 1000 3.4 -> 2.7, 3.3 -> 2.7.
+// M = 1000 3.4 -> 2.7, 3.3 -> 2.7.  Batches of few blocks have the rounds' waves to fill
+// the chip and their overlap with the middle products: from 1024 budgets on they keep
+// them (8 chains of L = 208, M = 1600 6.3 -> 7.3, 8.0 -> 9.1; 15 of L = 200, M = 1600
+// 9.3 -> 10.5, 12.3 -> 12.9; M = 1000 5.1 -> 4.6, 5.6 -> 5.4).
 constexpr int kTileEdgeBudgets = 1024, kTileEdgeBudgetsPerStage = 8;
 // Block-diagonals of so many blocks by tiles fill the chip by themselves: the next
 // one's inner products beside them lose (256 chains of L = 130, M = 1000 30.5 -> 32.3 ms,
@@ -2111,7 +2118,8 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
     const bool short_chains = tb.M >= 1024 && tb.M > kTileBudgetsPerStage * L;
     const uint64_t stream_max = nc > 1 ? (!tiles         ? kStreamMaxCandidatesN
                                           : short_chains ? kTileMaxCandidatesShortN
-                                                         : kTileMaxCandidatesN)
+                                          : L <= 128     ? kTileMaxCandidatesN
+                                                         : kTileMaxCandidatesLongN)
                                 : !tiles ? kStreamMaxCandidates1
                                 : tb.M < 256  ? kTileMaxCandidatesFew
                                 : tb.M < 1024 ? kTileMaxCandidates1
@@ -2152,8 +2160,10 @@ hipError_t launch_fill(const Tables &tb, const Work &w, int schedule, hipStream_
     // Edges of block-diagonal delta by tiles, 8 launches instead of 30.  From the
     // first such block-diagonal on all are (they have ever fewer blocks), so the
     // 2-byte copy, which the tiles' windows overwrite, is no longer read.
-    const bool edge_budgets = tb.M < kTileEdgeBudgets || tb.M <= kTileEdgeBudgetsPerStage * L ||
-                              (tb.M < 2 * kTileEdgeBudgets && tb.M <= kTileBudgetsPerStage * L);
+    const bool edge_budgets = tb.M < kTileEdgeBudgets ||
+                              ((tb.M <= kTileEdgeBudgetsPerStage * L ||
+                                (tb.M < 2 * kTileEdgeBudgets && tb.M <= kTileBudgetsPerStage * L)) &&
+                               (nc == 1 || (int64_t)(nb - 1) * tb.n_chains >= kAloneBlocks));
     auto tile_edges = [&](int delta) {
         return schedule != ROTOR_SCHEDULE_BLOCKED_ROWS && schedule != ROTOR_SCHEDULE_BLOCKED_ROUNDS && edge_budgets &&
                (r_total <= kTileEdgeCandidates || nb <= kTileEdgeBlocks ||

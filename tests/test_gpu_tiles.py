@@ -145,6 +145,21 @@ def test_many_budgets_are_not_filled_in_turn(n, L, M):
     assert ms < 2 * ms_rounds, (ms, ms_rounds)
 
 
+# the edges of a batch from 1024 budgets on: by rounds (29 or 30 launches per
+# block-diagonal) where it holds few blocks, by tiles (at most 10) where many
+@pytest.mark.parametrize("n,L,M,by_tiles", [(8, 200, 1500, False), (40, 120, 1100, True), (12, 200, 800, True)])
+def test_edges_of_batches(n, L, M, by_tiles):
+    from paper_1911_13214_amd import rotor
+
+    print(f"edges of batches n={n} L={L} M={M}", flush=True)
+    p = limited(n, L, M, 1350, 0.5)
+    stats = rotor.rotor_solve_timed(rotor.upload_params(p, M), n, L, M, *rotor.alloc_tables(n, L, M),
+                                    rotor.alloc_workspace(n, L, M))
+    diagonals = (L + 15) // 16 - 1
+    launches = stats["edge"]["launches"]
+    assert 8 * diagonals <= launches <= 10 * diagonals if by_tiles else launches >= 29 * diagonals
+
+
 # sizes past the windows' overlap cost a launch per window (0.25 and 0.48 ms against 0.21
 # and 0.35), not the windows of every tile in turn (0.48 and 1.2)
 @pytest.mark.parametrize("L,M", [(64, 1500), (100, 2400)])
